@@ -49,9 +49,12 @@
  *     the union of a 16-filter tile's items), kgs_order=0|1 (16-bit union
  *     with 4x4 groups: 4-filter blocks that keep similar items share a tile
  *     when that saves at least 5% of the K-steps by default; 1 = whenever it
- *     saves any, 0 = never).  Launch-time
+ *     saves any, 0 = never), wide=0 (no wide layout; so does any of the keys
+ *     above but the small_ ones).  Launch-time
  *     keys change the launch of a forward call: splits=N (input-channel
- *     splits) and wg_order=0|1 (workgroup order).  Results stay within the
+ *     splits), wg_order=0|1 (workgroup order), wide=1 (the wide kernel
+ *     wherever the blob and the input allow it), wide_fm=1|2 (its 32-filter
+ *     rows per wave) and wide_wm=1|2|4 (its waves along the filters).  Results stay within the
  *     documented accuracy under every setting.
  *   - Errors: all arguments are validated before anything is launched; on
  *     error nothing is written to the outputs and rt3d_last_error_detail()
@@ -209,7 +212,9 @@ rt3d_status rt3d_conv3d_workspace_size(const rt3d_conv3d_desc *desc,
  * weights (the 16-bit union may place 4-filter blocks that keep similar
  * items in the same tile; outputs land in layer order either way); the
  * 16-bit pair mapping packs two items whose kept groups
- * are disjoint into one 2:4 sparse MFMA slot and streams kept weights only.
+ * are disjoint into one 2:4 sparse MFMA slot and streams kept weights only;
+ * the wide 16-bit kernel, taken where it is modelled faster, multiplies every
+ * (16-channel slice, position) of a 64-filter tile, pruned weights as zeros.
  * Asynchronous on `stream`.  Per-call limits (RT3D_ERR_UNSUPPORTED,
  * checked before any launch; the same for rt3d_conv3d_dense_fwd): fewer
  * than 2^24 output voxels and 2^24 workgroups, and for layers packed onto

@@ -11,6 +11,7 @@
 #include <mutex>
 #include <numeric>
 #include <tuple>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -393,6 +394,8 @@ struct Layout {
   uint32_t variant = 0;
   std::vector<uint32_t> step_ptr, item_ptr, items, keep;
   std::vector<uint8_t> a;  // operand stream, raw element bytes
+  WidePlan wide{};         // c16 > 0: the blob also holds the wide layout
+  std::vector<uint8_t> wide_a;
 };
 
 // Element (filter m, channel c, position pos) of the dense weights, or zero
@@ -583,7 +586,7 @@ int kgs_tile_width(const Geom &g, const Tiling &tl, const Mask4 *m4) {
 // per_cu_split / per_cu_whole: resident workgroups per CU of split and
 // unsplit launches; cus: compute units.
 int model_splits(const Geom &g, const Tiling &tl, int mfw, double chunk_steps, uint32_t variant,
-                 long wgs, int per_cu_split, int per_cu_whole, long cus) {
+                 long wgs, int per_cu_split, int per_cu_whole, long cus, double *cycles = nullptr) {
   const long total_vox = static_cast<long>(g.n) * g.to * g.ho * g.wo;
   const double partial_bytes = 2.0 * static_cast<double>(total_vox) * ((g.c_out + 3) / 4 * 4) * 4;
   constexpr double kFixed = 12000, kReduce = 9600, kShare = 0.2, kPartialBytesPerCycle = 4200;
@@ -611,6 +614,7 @@ int model_splits(const Geom &g, const Tiling &tl, int mfw, double chunk_steps, u
       splits = s;
     }
   }
+  if (cycles) *cycles = best;
   return splits;
 }
 
@@ -1270,10 +1274,229 @@ void build_exact_f32_layout(const Geom &g, const Tiling &tl, const uint8_t *w, c
   }
 }
 
+// ---------------------------------------------------------------------------
+// Wide layout (16-bit): 32x32x16 MFMA fragments of the whole weight tensor
+// ---------------------------------------------------------------------------
+
+// Cycles a 16-lane set of a ds_read_b128 takes beyond one: the most distinct
+// rows (of an odd multiple of 16 bytes) that share a bank group, over the two
+// sets of every 32-slot fragment, averaged.
+double wide_conflict(const Geom &g, int bt, int bh, int bw, int hwp, int hpp, int slots) {
+  int total = 0;
+  for (int f = 0; f < slots / 16; ++f) {
+    int hits[16] = {0}, worst = 1;
+    for (int n = 0; n < 16; ++n) {
+      const int s = 16 * f + n, tt = s / (bh * bw), hh = (s / bw) % bh, ww = s % bw;
+      if (tt >= bt) continue;
+      const int r = (tt * g.st) * hpp + (hh * g.sh) * hwp + ww * g.sw;
+      worst = std::max(worst, ++hits[r & 15]);
+    }
+    total += worst;
+  }
+  return total / (slots / 16.0);
+}
+
+// Launch shape of the wide kernel for one call.
+struct WideLaunch {
+  int fm = 0;              // 32-filter rows per wave (0: the call takes the item kernel)
+  int wm = 0, wk = 0;      // waves along the filters, parts of the reduction
+  int splits = 1;          // channel-chunk splits across workgroups
+  uint64_t ws_bytes = 0;
+  int order = 0;
+  long wgs = 0;            // workgroups that run at once
+  double cycles = 0;       // modelled time
+};
+
+// The best launch shape of a wide plan, by a time model in cycles.  A
+// workgroup per CU walks its tiles one after the other; a tile is its chunks
+// (K-steps, or the loads of the next chunk where those take longer, and a
+// barrier) and its epilogue, a launch adds its start and the first chunk's
+// loads, splits add partial sums and their reduction.  The constants were
+// fitted to 110 layers of the C3D, R(2+1)D and S3D stacks at batch 1 to 32
+// (mean error 5.5%).
+WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cus, int want_splits,
+                     int want_fm, int want_wm) {
+  WideLaunch best;
+  best.wgs = cus;
+  const long bricks = static_cast<long>(g.n) * ((g.to + wp.bt - 1) / wp.bt) *
+                      ((g.ho + wp.bh - 1) / wp.bh) * ((g.wo + wp.bw - 1) / wp.bw);
+  const int c16_total = (g.c_in + 15) / 16, nch = (c16_total + wp.c16 - 1) / wp.c16;
+  const uint64_t per_split =
+      static_cast<uint64_t>(g.n) * g.to * g.ho * g.wo * ((g.c_out + 3) / 4 * 4) * 4;
+  const int rows32 = (g.c_out + 31) / 32;
+  const double rows = static_cast<double>((wp.bt - 1) * g.st + g.kt) * ((wp.bh - 1) * g.sh + g.kh) *
+                      ((wp.bw - 1) * g.sw + g.kw);
+  constexpr double kStep[3] = {0, 223, 349}, kTile[3] = {0, 7645, 12850};
+  constexpr double kLoad = 5.8, kLoadFree = 4817, kChunk = 670, kStart = 4450;
+  constexpr double kReduceStart = 4700, kPartialBytes = 0.63;   // per byte written and read back
+  const double load = kLoad * rows * wp.c16;
+  double best_t = -1;
+  for (int fm = 1; fm <= 2; ++fm) {
+    if (want_fm > 0 && want_fm != fm) continue;
+    const int tiles = (rows32 + fm - 1) / fm;
+    for (int wm = 1; wm <= 4; wm *= 2) {
+      if (wm > 1 && wm / 2 >= tiles) continue;   // half the waves would idle
+      if (want_wm > 0 && want_wm != wm) continue;
+      const int wk = 4 / wm;
+      const int chunk_steps = (g.ks * wp.c16 + wk - 1) / wk;
+      if (chunk_steps > kWideSteps) continue;
+      const long ntg = (tiles + wm - 1) / wm;
+      const double chunk = std::max(chunk_steps * kStep[fm], load - kLoadFree) + kChunk;
+      for (int per = nch; per >= 1;) {   // chunks per workgroup; s = ceil(nch / per) splits
+        const int s = (nch + per - 1) / per;
+        if (s > 1 && per_split * s > ws_cap) break;
+        const int want = want_splits > 0 ? std::min(nch, want_splits) : 0;
+        const long n = bricks * ntg * s;
+        if (n >= (1L << 24)) break;
+        if (!want || s <= want) {
+          double t = static_cast<double>((n + cus - 1) / cus) * (per * chunk + kTile[fm]) + kStart + load;
+          if (s > 1) t += kReduceStart + kPartialBytes / 1000 * 2.0 * static_cast<double>(s * per_split);
+          if (best_t < 0 || t < best_t || (want && s > best.splits)) {
+            best_t = t;
+            best.fm = fm;
+            best.wm = wm;
+            best.wk = wk;
+            best.splits = s;
+            best.ws_bytes = s > 1 ? per_split * s : 0;
+            best.cycles = t;
+          }
+        }
+        if (per == 1) break;
+        // the next smaller chunk count that changes the split count
+        const int next = (nch + s) / (s + 1);
+        per = next < per ? next : per - 1;
+      }
+    }
+  }
+  return best;
+}
+
+// Brick, halo pitches and chunk width of the wide kernel for this batch
+// size; a_off stays 0, c16 = 0 when nothing fits.  Among the bricks that
+// waste few slots, each with the pitch padding of the fewest LDS conflicts,
+// the launch model picks (a conflict costs about 4% of a step: the reads use
+// a quarter of the LDS rate).
+WidePlan wide_tiling(const Geom &g, int fn) {
+  WidePlan best{};
+  const int slots = 32 * fn, c16_total = (g.c_in + 15) / 16;
+  auto each_brick = [&](auto &&f) {
+    for (int bw = g.qw; bw <= std::max(g.qw, std::min(g.wo, slots)); bw += g.qw)
+      for (int bh = g.qh; bh <= std::max(g.qh, std::min(g.ho, slots / bw)); bh += g.qh)
+        for (int bt = g.qt; bt <= std::max(g.qt, std::min(g.to, slots / (bw * bh))); bt += g.qt) {
+          if (bt * bh * bw > slots) continue;
+          f(bt, bh, bw, static_cast<double>((g.to + bt - 1) / bt) * ((g.ho + bh - 1) / bh) * ((g.wo + bw - 1) / bw));
+        }
+  };
+  auto rows_of = [&](int bt, int bh, int bw) {
+    return static_cast<double>((bt - 1) * g.st + g.kt) * ((bh - 1) * g.sh + g.kh) * ((bw - 1) * g.sw + g.kw);
+  };
+  double min_nb = -1;
+  each_brick([&](int, int, int, double nb) { min_nb = min_nb < 0 ? nb : std::min(min_nb, nb); });
+  double min_rows = -1;   // smallest halo among the bricks that waste few slots
+  each_brick([&](int bt, int bh, int bw, double nb) {
+    if (nb <= 1.15 * min_nb) min_rows = min_rows < 0 ? rows_of(bt, bh, bw) : std::min(min_rows, rows_of(bt, bh, bw));
+  });
+  double best_t = -1;
+  each_brick([&](int bt, int bh, int bw, double nb) {
+    if (nb > 1.15 * min_nb || rows_of(bt, bh, bw) > 1.6 * min_rows) return;
+    const int ht = (bt - 1) * g.st + g.kt, hh = (bh - 1) * g.sh + g.kh, hw = (bw - 1) * g.sw + g.kw;
+    if (ht > 511 || hh > 511 || hw > 511) return;   // 9 bits each in the stage table
+    double conf = -1;
+    int hwp = hw, hpp = hh * hw;
+    for (int pw = 0; pw < 4; ++pw)
+      for (int pp = 0; pp < 4; ++pp) {
+        const double c = wide_conflict(g, bt, bh, bw, hw + pw, hh * (hw + pw) + pp, slots) +
+                         0.3 * (static_cast<double>(ht) * (hh * (hw + pw) + pp) / (static_cast<double>(ht) * hh * hw) - 1);
+        if (conf < 0 || c < conf) {
+          conf = c;
+          hwp = hw + pw;
+          hpp = hh * hwp + pp;
+        }
+      }
+    const long rows = static_cast<long>(ht) * hpp;
+    if (hpp > 65535 || rows > 4096) return;
+    for (int c16 = 1; c16 <= std::min(8, c16_total); ++c16) {
+      const long row = c16 * 32 + 16;
+      if (2 * rows * row + kWideFixedLds > kWideLds || rows * (row / 16) > 11 * 256) break;
+      WidePlan wp{};
+      wp.bt = static_cast<uint8_t>(bt);
+      wp.bh = static_cast<uint8_t>(bh);
+      wp.bw = static_cast<uint8_t>(bw);
+      wp.c16 = static_cast<uint8_t>(c16);
+      wp.hwp = static_cast<uint16_t>(hwp);
+      wp.hpp = static_cast<uint16_t>(hpp);
+      wp.fn = static_cast<uint8_t>(fn);
+      Geom one = g;
+      one.n = std::max(g.n, 1);
+      const WideLaunch L = best_wide(one, wp, kScratchBytes, 256, 0, 0, 0);
+      if (L.fm == 0) continue;
+      const double t = L.cycles * (1.0 + 0.04 * (conf - 1.0));
+      if (best_t < 0 || t < best_t) {
+        best_t = t;
+        best = wp;
+      }
+    }
+  });
+  return best;
+}
+
+// Does a pack write the wide layout?  16-bit layers off the small-channel
+// kernel, unless a tuning switch names an item-kernel layout.
+bool wide_wanted(const Geom &g, bool small, const Mask4 *m4) {
+  if (g.es != 2 || small || g.c_in < 16) return false;
+  const int v = tune("wide");
+  if (v == 0) return false;
+  for (const char *key : {"slots", "kgs_mfw", "dense_mfw", "kgs_map", "pair_mfw", "cc", "kgs_order"})
+    if (tune(key) >= 0) return false;
+  // the weight section is addressed with 31 bits
+  if (static_cast<double>((g.c_out + 63) / 64 * 64) * g.ks * ((g.c_in + 15) / 16 * 16) * 2 >= 2.1e9) return false;
+  (void)m4;
+  return true;
+}
+
+// Steps in blob order (chunks, kernel positions, 16-channel slices).
+void build_wide_layout(const Geom &g, const WidePlan &wp, const uint8_t *w, const Mask4 *m4,
+                       std::vector<uint8_t> &out) {
+  const int c16_total = (g.c_in + 15) / 16;
+  const int frags = ((g.c_out + 31) / 32 + 1) / 2 * 2;
+  const long stot = static_cast<long>(g.ks) * c16_total;
+  out.assign(static_cast<size_t>(frags) * stot * 1024, 0);
+  std::vector<long> step_of(stot);   // [c16 slice][pos] -> step
+  {
+    long s = 0;
+    for (int c0 = 0; c0 < c16_total; c0 += wp.c16)
+      for (int pos = 0; pos < g.ks; ++pos)
+        for (int c = c0; c < std::min(c16_total, c0 + wp.c16); ++c) step_of[static_cast<long>(c) * g.ks + pos] = s++;
+  }
+  const uint16_t *src = reinterpret_cast<const uint16_t *>(w);
+  uint16_t *dst = reinterpret_cast<uint16_t *>(out.data());
+  for (int m = 0; m < g.c_out; ++m)
+    for (int c = 0; c < g.c_in; ++c) {
+      const uint16_t *row = src + (static_cast<size_t>(m) * g.c_in + c) * g.ks;
+      const long lane = (m & 31) + 32 * ((c >> 3) & 1);
+      const long base = (m >> 5) * stot * 512 + lane * 8 + (c & 7);
+      const long *so = &step_of[static_cast<long>(c >> 4) * g.ks];
+      const uint8_t *mk = m4 ? m4->mask + (static_cast<size_t>(m / 4 / m4->gm4) * m4->Q + c / 4 / m4->gn4) * g.ks : nullptr;
+      for (int pos = 0; pos < g.ks; ++pos)
+        if (!mk || mk[pos]) dst[base + so[pos] * 512] = row[pos];
+    }
+  // Stage table: where each 16-byte slot of a halo buffer comes from.
+  const int hh = (wp.bh - 1) * g.sh + g.kh, hw = (wp.bw - 1) * g.sw + g.kw, spr = wp.c16 * 2 + 1;
+  const int ht = (wp.bt - 1) * g.st + g.kt;
+  for (int r = 0; r < ht * wp.hpp; ++r) {
+    const uint32_t t = r / wp.hpp, h = r % wp.hpp / wp.hwp, w2 = r % wp.hpp % wp.hwp;
+    for (int p = 0; p < spr; ++p) {
+      const bool real = static_cast<int>(h) < hh && static_cast<int>(w2) < hw && p < spr - 1;
+      const uint32_t e = real ? t | h << 9 | w2 << 18 | static_cast<uint32_t>(p) << 27 : ~0u;
+      out.insert(out.end(), reinterpret_cast<const uint8_t *>(&e), reinterpret_cast<const uint8_t *>(&e) + 4);
+    }
+  }
+}
+
 // Assemble header + canonical + layout sections.  With out == nullptr only
 // the size is computed.
 struct Sections {
-  uint64_t header, canon[4], step_ptr, item_ptr, items, keep, a, total;
+  uint64_t header, canon[4], step_ptr, item_ptr, items, keep, a, wide, total;
 };
 
 Sections section_offsets(const Canon *c, int es, const Layout &L) {
@@ -1298,6 +1521,8 @@ Sections section_offsets(const Canon *c, int es, const Layout &L) {
   off = align_up(off + L.keep.size() * 4, kAlign);
   s.a = off;
   off = align_up(off + L.a.size(), kAlign);
+  s.wide = off;
+  off = align_up(off + L.wide_a.size(), kAlign);
   s.total = off;
   return s;
 }
@@ -1335,6 +1560,11 @@ void fill_info(const rt3d_conv3d_desc *d, const Canon *c, const Layout &L, const
   p.a_off = s.a;
   p.keep_off = s.keep;
   std::memcpy(info->plan, &p, sizeof(p));
+  if (!L.wide_a.empty()) {
+    WidePlan wp = L.wide;
+    wp.a_off = s.wide;
+    std::memcpy(reinterpret_cast<uint8_t *>(info->plan) + sizeof(p), &wp, sizeof(wp));
+  }
 }
 
 void write_blob(uint8_t *out, const rt3d_pack_info &info, const Canon *c, const uint8_t *w,
@@ -1371,6 +1601,7 @@ void write_blob(uint8_t *out, const rt3d_pack_info &info, const Canon *c, const 
   if (!L.items.empty()) std::memcpy(out + s.items, L.items.data(), L.items.size() * 4);
   if (!L.keep.empty()) std::memcpy(out + s.keep, L.keep.data(), L.keep.size() * 4);
   if (!L.a.empty()) std::memcpy(out + s.a, L.a.data(), L.a.size());
+  if (!L.wide_a.empty()) std::memcpy(out + s.wide, L.wide_a.data(), L.wide_a.size());
 }
 
 // 16-bit KGS mapping: pairs (2:4 sparse MFMA over 64-slot bricks) or the
@@ -1416,6 +1647,13 @@ int pair_width(const Geom &g, const Mask4 *m4) {
   (void)m4;
   const int v = tune("pair_mfw");
   return (v == 2 || v == 4) ? v : 1;
+}
+
+// Adds the wide layout where the planner wants one.
+void add_wide(const Geom &g, bool small, const uint8_t *w, const Mask4 *m4, Layout &L) {
+  if (!wide_wanted(g, small, m4)) return;
+  L.wide = wide_tiling(g, 4);
+  if (L.wide.c16 > 0 && (g.c_in + 15) / 16 / L.wide.c16 < 4000) build_wide_layout(g, L.wide, w, m4, L.wide_a);
 }
 
 // Build everything for a KGS pack (w may be null when only sizing).
@@ -1470,6 +1708,7 @@ rt3d_status plan_kgs(const rt3d_conv3d_desc *d, const uint8_t *mask, const uint8
       build_pairs_layout(g, tl, wsrc, &m4, L, pair_width(g, &m4));
     } else {
       build_items_layout(g, tl, wsrc, &m4, L, small, ip.mfw);
+      add_wide(g, small, wsrc, &m4, L);
     }
   }
   return ok();
@@ -1605,7 +1844,7 @@ Launch plan_launch(const rt3d_conv3d_desc *d, const Plan &p, uint32_t variant, u
   const Tiling &tl = p.tiling;
   const long bricks = static_cast<long>(g.n) * ((g.to + tl.bt - 1) / tl.bt) *
                       ((g.ho + tl.bh - 1) / tl.bh) * ((g.wo + tl.bw - 1) / tl.bw);
-  Launch L{4, 1, 0, 0};
+  Launch L{4, 1, 0, 0, 0};
   if (variant == kVarSmallDense16 || variant == kVarSmallKgs16) return L;  // one chunk, no split
   const long ntg = (p.wave_tiles + L.wpw - 1) / L.wpw;
   const long wgs = bricks * ntg;
@@ -1621,7 +1860,7 @@ Launch plan_launch(const rt3d_conv3d_desc *d, const Plan &p, uint32_t variant, u
   if (per_cu_whole <= 0) per_cu_whole = per_cu_split;
   const double chunk_steps = p.tile_steps > 0 ? static_cast<double>(p.tile_steps) / tl.nchunks : 24.0;
   int splits = model_splits(g, tl, p.mfw, chunk_steps, variant, wgs, per_cu_split, per_cu_whole,
-                            device_cus());
+                            device_cus(), &L.cycles);
   if (tune("splits") > 0) splits = std::max(1, std::min(tl.nchunks, tune("splits")));
   const long total_vox = static_cast<long>(g.n) * g.to * g.ho * g.wo;
   const uint64_t per_split = static_cast<uint64_t>(total_vox) * ((g.c_out + 3) / 4 * 4) * 4;
@@ -1632,6 +1871,46 @@ Launch plan_launch(const rt3d_conv3d_desc *d, const Plan &p, uint32_t variant, u
   const double x_unit = static_cast<double>(tl.ht) * tl.hh * tl.hw * tl.cc * g.es * tl.nchunks / splits;
   L.order = xcd_fill_bytes(bricks, ntg, splits, 1, a_unit, x_unit) <
                     xcd_fill_bytes(bricks, ntg, splits, 0, a_unit, x_unit)
+                ? 1
+                : 0;
+  if (tune("wg_order") >= 0) L.order = tune("wg_order") ? 1 : 0;
+  return L;
+}
+
+WidePlan wide_plan_of(const rt3d_pack_info *info) {
+  WidePlan wp;
+  std::memcpy(&wp, reinterpret_cast<const uint8_t *>(info->plan) + sizeof(Plan), sizeof(wp));
+  return wp;
+}
+
+// The wide kernel's launch for this call, fm = 0 when the call runs on the
+// item kernel: no wide layout in the blob, an input pitch or offset that is
+// not a multiple of 8 channels (the staging loads whole 16-byte pieces), a
+// batch item of 4 GiB or more (32-bit halo offsets), or an item-kernel launch
+// that is modelled faster.  The item kernel's model was fitted like the wide
+// one's (its own cycles x 0.73 plus 1.06 us per million outputs, 10% mean
+// error); the 5% margin keeps the item kernel where the two are close.
+WideLaunch plan_wide(const rt3d_conv3d_desc *d, const WidePlan &wp, uint64_t ws_cap,
+                     double item_cycles) {
+  WideLaunch none;
+  if (wp.a_off == 0) return none;
+  const int x_pitch = d->x_c_total != 0 ? d->x_c_total : d->c_in;
+  if (x_pitch % 8 != 0 || d->x_c_off % 8 != 0) return none;
+  const Geom g = geom_of(d);
+  if (static_cast<double>(g.t) * g.h * g.w * x_pitch * 2 >= 4.29e9) return none;
+  WideLaunch L = best_wide(g, wp, std::min<uint64_t>(ws_cap, kScratchBytes), device_cus(),
+                           tune("splits"), tune("wide_fm"), tune("wide_wm"));
+  if (L.fm == 0) return none;
+  const double outputs = static_cast<double>(g.n) * g.to * g.ho * g.wo * g.c_out;
+  if (tune("wide") != 1 && 0.73 * item_cycles + 2383e-6 * outputs < 1.05 * L.cycles) return none;
+  const long bricks = static_cast<long>(g.n) * ((g.to + wp.bt - 1) / wp.bt) *
+                      ((g.ho + wp.bh - 1) / wp.bh) * ((g.wo + wp.bw - 1) / wp.bw);
+  const int c16_total = (g.c_in + 15) / 16, rows32 = (g.c_out + 31) / 32;
+  const long ntg = ((rows32 + L.fm - 1) / L.fm + L.wm - 1) / L.wm;
+  const double a_unit = static_cast<double>(rows32) * 1024 * g.ks * c16_total / (static_cast<double>(ntg) * L.splits);
+  const double x_unit = static_cast<double>(wp.hpp) * ((wp.bt - 1) * g.st + g.kt) * c16_total * 32.0 / L.splits;
+  L.order = xcd_fill_bytes(bricks, ntg, L.splits, 1, a_unit, x_unit) <
+                    xcd_fill_bytes(bricks, ntg, L.splits, 0, a_unit, x_unit)
                 ? 1
                 : 0;
   if (tune("wg_order") >= 0) L.order = tune("wg_order") ? 1 : 0;
@@ -1656,6 +1935,8 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   Plan p;
   std::memcpy(&p, info->plan, sizeof(p));
   const Launch launch = plan_launch(d, p, info->variant, workspace ? ws_bytes : 0, info->packed_bytes - p.a_off);
+  const WidePlan wp = wide_plan_of(info);
+  const WideLaunch wl = plan_wide(d, wp, workspace ? ws_bytes : 0, launch.cycles);
   const Geom g = geom_of(d);
   const Tiling &tl = p.tiling;
   const uint8_t *b = static_cast<const uint8_t *>(blob);
@@ -1713,6 +1994,42 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   if (static_cast<long>(a.n) * a.nbt * a.nbh * a.nbw * a.ntg * a.splits >= (1L << 24))
     return fail(RT3D_ERR_UNSUPPORTED, "layer needs 2^24 or more workgroups");
   int e;
+  if (wl.fm > 0) {
+    WideArgs wa{};
+    static_cast<ConvArgs &>(wa) = a;
+    wa.a = b + wp.a_off;
+    wa.stage_tab = reinterpret_cast<const uint32_t *>(
+        b + wp.a_off + static_cast<uint64_t>(((g.c_out + 31) / 32 + 1) / 2 * 2) * g.ks * ((g.c_in + 15) / 16) * 1024);
+    wa.a_bytes = ((g.c_out + 31) / 32 + 1) / 2 * 2 * g.ks * ((g.c_in + 15) / 16) * 1024;
+    wa.bt = wp.bt; wa.bh = wp.bh; wa.bw = wp.bw;
+    wa.nbt = (g.to + wp.bt - 1) / wp.bt;
+    wa.nbh = (g.ho + wp.bh - 1) / wp.bh;
+    wa.nbw = (g.wo + wp.bw - 1) / wp.bw;
+    wa.ht = (wp.bt - 1) * g.st + g.kt;
+    wa.hh = (wp.bh - 1) * g.sh + g.kh;
+    wa.hw = (wp.bw - 1) * g.sw + g.kw;
+    wa.hwp = wp.hwp; wa.hpp = wp.hpp;
+    wa.c16 = wp.c16;
+    wa.c16_total = (g.c_in + 15) / 16;
+    wa.nchunks = (wa.c16_total + wp.c16 - 1) / wp.c16;
+    wa.row = wp.c16 * 32 + 16;
+    wa.kh = g.kh; wa.kw = g.kw; wa.ks = g.ks;
+    wa.stot = g.ks * wa.c16_total;
+    wa.splits = wl.splits;
+    wa.order = wl.order;
+    wa.wave_tiles = ((g.c_out + 31) / 32 + wl.fm - 1) / wl.fm;
+    wa.ntg = (wa.wave_tiles + wl.wm - 1) / wl.wm;
+    wa.nbricks = static_cast<int32_t>(static_cast<long>(g.n) * wa.nbt * wa.nbh * wa.nbw);
+    wa.buf_bytes = wa.ht * wa.hpp * wa.row;
+    wa.lds_bytes = 2 * wa.buf_bytes + kWideFixedLds;
+    // one workgroup per CU; each walks tiles id, id + grid, ...
+    wa.grid = static_cast<int32_t>(std::min<long>(static_cast<long>(wa.nbricks) * wa.ntg * wa.splits, wl.wgs));
+    e = launch_wide16(wa, d->dtype, wl.fm, wl.wk, stream);
+    if (e == hipSuccess && wa.splits > 1) e = launch_reduce_splits(wa, d->dtype, stream);
+    if (e != hipSuccess)
+      return fail(RT3D_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(static_cast<hipError_t>(e)));
+    return ok();
+  }
   switch (info->variant) {
     case kVarDenseItems16:
     case kVarKgsUnion16:
@@ -1934,7 +2251,9 @@ rt3d_status rt3d_conv3d_workspace_size(const rt3d_conv3d_desc *d, const rt3d_pac
     return fail(RT3D_ERR_BLOB_MISMATCH, "info does not belong to this layer description");
   Plan p;
   std::memcpy(&p, info->plan, sizeof(p));
-  *bytes = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off).ws_bytes;
+  const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off);
+  // enough for either kernel (the input's pitch may rule the wide one out)
+  *bytes = std::max(L.ws_bytes, plan_wide(d, wide_plan_of(info), UINT64_MAX, L.cycles).ws_bytes);
   return ok();
 }
 
@@ -1957,7 +2276,9 @@ rt3d_status rt3d_kgs_conv3d_fwd_noalloc(const rt3d_conv3d_desc *d, const rt3d_pa
   std::memcpy(&p, info->plan, sizeof(p));
   // The split count a caller workspace of any size would get: the launch is
   // then the one rt3d_kgs_conv3d_fwd makes with that workspace.
-  const uint64_t need = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off).ws_bytes;
+  const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off);
+  const uint64_t need =
+      std::max(L.ws_bytes, plan_wide(d, wide_plan_of(info), UINT64_MAX, L.cycles).ws_bytes);
   if (need > kScratchBytes)
     return fail(RT3D_ERR_UNSUPPORTED,
                 "this launch needs %llu bytes of split-K scratch; the no-allocation entry point "
@@ -1983,6 +2304,7 @@ rt3d_status rt3d_dense_pack_size(const rt3d_conv3d_desc *d, uint64_t *bytes) {
   std::vector<uint8_t> scratch(static_cast<size_t>(g.c_out) * g.c_in * g.ks * g.es, 0);
   Layout L;
   build_items_layout(g, tl, scratch.data(), nullptr, L, small, ip.mfw);
+  add_wide(g, small, scratch.data(), nullptr, L);
   *bytes = section_offsets(nullptr, g.es, L).total;
   return ok();
 }
@@ -2000,6 +2322,7 @@ rt3d_status rt3d_dense_pack(const rt3d_conv3d_desc *d, const void *w_dense, void
   if (tl.cc == 0) return fail(RT3D_ERR_UNSUPPORTED, "no voxel tiling fits in LDS for this layer");
   Layout L;
   build_items_layout(g, tl, static_cast<const uint8_t *>(w_dense), nullptr, L, small, ip.mfw);
+  add_wide(g, small, static_cast<const uint8_t *>(w_dense), nullptr, L);
   const Sections s = section_offsets(nullptr, g.es, L);
   if (blob_bytes < s.total)
     return fail(RT3D_ERR_BUFFER_TOO_SMALL, "blob needs %llu bytes, got %llu",

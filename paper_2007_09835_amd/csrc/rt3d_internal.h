@@ -101,12 +101,50 @@ struct ConvArgs {
   int32_t gmap_slots; // entries of gmap (wave_tiles * 4 * mfw)
 };
 
+// Second layout of a 16-bit blob, for the wide kernel (kept in the rest of
+// rt3d_pack_info::plan; a_off = 0 when the blob has none).  The weights are
+// MFMA fragments of 32 filters x 16 channels in lane order, [32-filter row]
+// [step][lane][8], rows padded to an even count with zeros; steps run over
+// channel chunks of 16 * c16 channels, then kernel positions, then the
+// chunk's 16-channel slices.
+// After the weights: the stage table, u32 per 16-byte slot of a halo buffer,
+// t | h << 9 | w << 18 | piece << 27 in the halo, all ones for padding.
+struct WidePlan {
+  uint64_t a_off;
+  uint8_t bt, bh, bw;      // output brick
+  uint8_t c16;             // 16-channel slices per chunk
+  uint16_t hwp, hpp;       // halo pitches in voxels: per row of w, per plane of (h, w)
+  uint8_t fn;              // 32-slot voxel fragments per brick
+  uint8_t reserved[7];
+};
+static_assert(sizeof(Plan) + sizeof(WidePlan) <= sizeof(((rt3d_pack_info *)0)->plan),
+              "plans do not fit");
+
+struct WideArgs : ConvArgs {
+  const uint32_t *stage_tab;  // see WidePlan
+  int32_t hwp, hpp;        // as in WidePlan
+  int32_t kh, kw, ks;      // kernel extent
+  int32_t c16, c16_total;  // 16-channel slices per chunk and of the layer
+  int32_t stot;            // K-steps of the layer: ks * c16_total
+  int32_t buf_bytes;       // one halo buffer
+  int32_t lds_bytes;       // dynamic LDS of the launch
+};
+
+constexpr int kWideSteps = 128;   // most K-steps of one part and chunk
+// LDS of the wide kernel: two halo buffers, the epilogue tile of four waves
+// (rows of 32 fp32 filters and 16 bytes), and two sets of epilogue tables
+// (output and first slot of 128 slots, bias of up to 256 filters).
+constexpr int kWideTileRow = 32 * 4 + 16;
+constexpr int kWideFixedLds = 4 * 128 * kWideTileRow + 2 * (128 * 8 + 256 * 4);
+constexpr int kWideLds = 160 * 1024;
+
 // Launch shape chosen at forward time from the batch size.
 struct Launch {
   int wpw;
   int splits;
   uint64_t ws_bytes;
   int order;  // ConvArgs::order
+  double cycles;  // modelled time
 };
 
 // Group norms / reweighted group-lasso penalty (Section 4).  A workgroup owns
@@ -138,6 +176,7 @@ void *noalloc_scratch();
 // with `lds` bytes of dynamic LDS each; 0 when the runtime cannot say.
 int conv_resident(int variant, int dtype, int mfw, int nf, size_t lds);
 int launch_items16(const ConvArgs &a, int dtype, int mfw, int map, void *stream);
+int launch_wide16(const WideArgs &a, int dtype, int fm, int wk, void *stream);
 int launch_small16(const ConvArgs &a, int dtype, int mfw, void *stream);
 size_t small_lds_bytes(const ConvArgs &a);
 int small_resident(const ConvArgs &a, int dtype, int mfw);

@@ -35,6 +35,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(__bf16)))) __bf16 bf16x16;
 typedef __attribute__((__vector_size__(16 * sizeof(_Float16)))) _Float16 f16x16;
 typedef __attribute__((__vector_size__(8 * sizeof(unsigned)))) unsigned u32x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 
 template <int... Is, typename F>
@@ -1022,6 +1023,534 @@ __global__ __launch_bounds__(256, (MAP != 0 || NF == 4 || MFW == 2) ? 2 : 1) voi
   }
   __syncthreads();
   tile_store<T>(a, b, lds, m_wg0);
+}
+
+// ---------------------------------------------------------------------------
+// Wide 16-bit kernel: v_mfma_f32_32x32x16_{bf16,f16}, the dense contraction
+// over every kernel position (KGS layers run it with their pruned weights as
+// zeros where a 64-filter tile keeps nearly every position anyway).
+//
+// A workgroup owns a brick of 32*FN output voxel slots and WM wave tiles of
+// 32*FM filters.  Waves 0-3 compute, split into WM filter tiles x WK parts of
+// the reduction (WM * WK = 4); waves 4-7 stage the input.  A K-step is 16
+// input channels at one kernel position: a lane reads its voxel's 16 bytes
+// (8 channels; lane half h = lane / 32 takes the upper 8) with one
+// ds_read_b128 -- twice the LDS rate of the item kernel's 8-byte reads -- at
+// its voxel's row plus an offset that is the same for the whole wave.  Each
+// step feeds FM*FN MFMAs of 32 cycles from FM weight fragments (global
+// memory, MFMA lane order, prefetched DA steps ahead) and FN voxel fragments.
+//
+// Channel chunks are double-buffered in LDS.  The staging waves write them by
+// direct global-to-LDS loads, so that the compute waves' memory counter holds
+// weight loads only: vector memory returns in order, and a halo load ahead of
+// a weight load would make the MFMAs wait for the slower one.  One barrier
+// per chunk.  The WK parts are added in the epilogue through LDS in a fixed
+// order.
+// ---------------------------------------------------------------------------
+
+// Voxel slot (within a 32-slot fragment) of lane l < 32.  A ds_read_b128 is
+// served 16 lanes at a time, lanes {0-3, 12-15, 20-27} and {4-11, 16-19,
+// 28-31} of each half (measured); this order gives each such set 16
+// consecutive slots.
+__device__ __forceinline__ int lane_slot(int l) {
+  return static_cast<int>((0x73261540u >> (l & 28)) & 7u) * 4 + (l & 3);
+}
+
+// One 16-byte direct load per active lane into LDS at lds + 16 * lane (lds is
+// wave-uniform; inactive lanes leave their 16 bytes alone).
+__device__ __forceinline__ void load_to_lds(const uint8_t *src, uint8_t *lds) {
+  __builtin_amdgcn_global_load_lds(
+      (const __attribute__((address_space(1))) void *)src,
+      (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+}
+
+// Workgroup barrier of the wide kernel.  Every LDS access of the wave is done
+// first; with VM its vector-memory loads (direct-to-LDS writes) are too.
+template <bool VM>
+__device__ __forceinline__ void wide_barrier() {
+  if constexpr (VM) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+constexpr int kWidePieces = 11;  // direct loads per staging lane and chunk (at most 44 KB)
+
+template <typename T, int FM, int FN, int WK>
+__global__ __launch_bounds__(512, 2) void wide_kernel(WideArgs a) {
+  using V8 = std::conditional_t<std::is_same_v<T, __bf16>, bf16x8, f16x8>;
+  constexpr int SLOTS = 32 * FN;
+  constexpr int WM = 4 / WK;
+  constexpr int DA = 6;                       // weight ring (steps); even
+  constexpr int TROW = kWideTileRow;          // epilogue tile: bytes per slot (32 filters)
+  constexpr int MWG = 32 * FM * WM;           // filters per workgroup
+  extern __shared__ __align__(16) uint8_t lds[];
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lane = tid & 63;
+  const int wave = uniform(tid >> 6);
+  const int buf_bytes = a.buf_bytes;
+  const int ntiles = a.nbricks * a.ntg * a.splits;
+  const int nwg = static_cast<int>(gridDim.x);
+  uint8_t *tile_lds = lds + 2 * buf_bytes;
+  // Per tile parity: output index of each (pooled) slot of the brick (~0:
+  // none) and its first slot; then the bias.
+  int2 *tables = reinterpret_cast<int2 *>(tile_lds + 4 * SLOTS * TROW);
+  constexpr int TAB = SLOTS + MWG / 2;        // entries of one parity, the bias included
+
+  auto tile_of = [&](int id) __attribute__((always_inline)) {   // this workgroup's tiles: id, id + nwg, ...
+    const int q = ntiles >> 3, r = ntiles & 7, xcd = id & 7, local = id >> 3;
+    return decode_tile(a, xcd < r ? xcd * (q + 1) + local : r * (q + 1) + (xcd - r) * q + local);
+  };
+
+  if (wave >= 4) {
+    // ---- staging waves ----
+    const int st = tid - 256;
+    const int spr = a.row >> 4;                // 16-byte slots per row (the last is padding)
+    const int npieces = buf_bytes >> 4;
+    // 16-byte slot p of a buffer is piece p % spr of halo row p / spr; a wave
+    // instruction covers 64 consecutive slots.  The blob's stage table holds
+    // each slot's place in the halo (t | h << 9 | w << 18 | piece << 27, all
+    // ones for padding): deriving it here took 2500-4400 of the 7000-10000
+    // cycles before the first loads went out.
+    uint32_t code[kWidePieces], off[kWidePieces];
+#pragma unroll
+    for (int k = 0; k < kWidePieces; ++k) code[k] = off[k] = ~0u;
+#pragma unroll
+    for (int k = 0; k < kWidePieces; ++k) {
+      if (k * 256 >= npieces) break;   // (leaves the unrolled code at once: it may not be cached yet)
+      if (st + k * 256 < npieces) code[k] = a.stage_tab[st + k * 256];
+    }
+    uint32_t pads = 0;               // bit k: this wave's instruction k has slots outside the clip
+    int buf = 0;                     // buffer of the next chunk
+    const uint8_t *xb = nullptr;
+    // Issues the loads of channel chunk ch of the current brick (slots
+    // outside the clip become zeros) into the next buffer.
+    auto stage = [&](int ch) __attribute__((always_inline)) {
+      const int c0 = ch * a.c16 * 16;
+      const uint8_t *src = xb + c0 * 2;
+      uint8_t *dst = lds + buf * buf_bytes;
+      if (c0 + a.c16 * 16 <= a.c_in) {   // every piece holds channels of the layer
+#pragma unroll
+        for (int k = 0; k < kWidePieces; ++k) {
+          if (k * 256 >= npieces) break;
+          if (off[k] != ~0u) load_to_lds(src + off[k], dst + (k * 256 + (wave - 4) * 64) * 16);
+          if ((pads >> k) & 1u) {
+            if (code[k] != ~0u && off[k] == ~0u)
+              *reinterpret_cast<uint4 *>(dst + (st + k * 256) * 16) = make_uint4(0, 0, 0, 0);
+          }
+        }
+        buf ^= 1;
+        return;
+      }
+#pragma unroll
+      for (int k = 0; k < kWidePieces; ++k) {
+        if (k * 256 >= npieces) break;
+        const int c = c0 + static_cast<int>(code[k] >> 27) * 8;
+        if (off[k] != ~0u && c < a.c_in)
+          load_to_lds(src + off[k], dst + (k * 256 + (wave - 4) * 64) * 16);
+        else if (code[k] != ~0u && (off[k] == ~0u || (c & ~15) < a.c_in))
+          // padding, or the upper half of the last 16-channel slice
+          *reinterpret_cast<uint4 *>(dst + (st + k * 256) * 16) = make_uint4(0, 0, 0, 0);
+      }
+      // A channel count that is not a multiple of 8: the last piece's extra
+      // channels (another layer's, or padding of the pitch) become zeros.
+      const int cut = (a.c_in >> 3) - ch * a.c16 * 2;
+      if ((a.c_in & 7) && cut >= 0 && cut < spr - 1) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int k = 0; k < kWidePieces; ++k) {
+          if (k * 256 >= npieces) break;
+          if (off[k] != ~0u && static_cast<int>(code[k] >> 27) == cut) {
+            uint4 *q = reinterpret_cast<uint4 *>(dst + (st + k * 256) * 16);
+            *q = cut_piece<2>(*q, a.c_in & 7);
+          }
+        }
+      }
+      buf ^= 1;
+    };
+    // Points the loads at a tile's brick.
+    auto aim = [&](const Brick &b) __attribute__((always_inline)) {
+      pads = 0;
+      xb = static_cast<const uint8_t *>(a.x) +
+           (static_cast<long>(b.nb) * a.t * a.h * a.w * a.x_pitch + a.x_off) * 2;
+#pragma unroll
+      for (int k = 0; k < kWidePieces; ++k) {
+        if (k * 256 >= npieces) break;
+        const uint32_t e = code[k];
+        const int zt = b.zt0 + static_cast<int>(e & 511u), zh = b.zh0 + static_cast<int>((e >> 9) & 511u),
+                  zw = b.zw0 + static_cast<int>((e >> 18) & 511u);
+        const bool in = (e != ~0u) & (static_cast<unsigned>(zt) < static_cast<unsigned>(a.t)) &
+                        (static_cast<unsigned>(zh) < static_cast<unsigned>(a.h)) &
+                        (static_cast<unsigned>(zw) < static_cast<unsigned>(a.w));
+        off[k] = in ? static_cast<uint32_t>((zt * a.h + zh) * a.w + zw) * static_cast<uint32_t>(a.x_pitch * 2) + (e >> 27) * 16u : ~0u;
+        pads |= __any(!in && e != ~0u) ? 1u << k : 0u;
+      }
+    };
+    auto fill_tables = [&](const Wg &wg, const Brick &b, int parity) __attribute__((always_inline)) {
+      int2 *outtab = tables + parity * TAB;
+      float *biastab = reinterpret_cast<float *>(outtab + SLOTS);
+      const bool pool = a.splits == 1;
+      const int qt = pool ? a.qt : 1, qh = pool ? a.qh : 1, qw = pool ? a.qw : 1;
+      if (st < SLOTS) {
+        const int pbt = divmod(a.bt, qt).q, pbh = divmod(a.bh, qh).q, pbw = divmod(a.bw, qw).q;
+        const DivMod x = divmod(st, pbh * pbw), y = divmod(x.r, pbw);
+        const int gt = divmod(b.ot0, qt).q + x.q, gh = divmod(b.oh0, qh).q + y.q, gw = divmod(b.ow0, qw).q + y.r;
+        const int eto = pool ? a.pto : a.to, eho = pool ? a.pho : a.ho, ewo = pool ? a.pwo : a.wo;
+        const bool ok = x.q < pbt && gt < eto && gh < eho && gw < ewo;
+        outtab[st] = make_int2(ok ? ((b.nb * eto + gt) * eho + gh) * ewo + gw : -1,
+                               ok ? (x.q * qt * a.bh + y.q * qh) * a.bw + y.r * qw : 0);
+      }
+      if (st < MWG) {
+        const int f = wg.tg * MWG + st;
+        biastab[st] = a.bias && f < a.c_out ? a.bias[f] : 0.f;
+      }
+    };
+    int id = static_cast<int>(blockIdx.x), parity = 0;
+    Wg wg = tile_of(id);
+    Brick b = decode_brick(a, wg.brick);
+    int ch0, ch1;
+    split_range(a, wg.split, ch0, ch1);
+    aim(b);
+    stage(ch0);
+    for (;;) {
+      // The epilogue's tables go out behind the second chunk's loads (or with
+      // the only chunk): the first barrier is what the compute waves wait for.
+      if (ch0 + 1 == ch1) fill_tables(wg, b, parity);
+      wide_barrier<true>();
+      for (int ch = ch0 + 1; ch < ch1; ++ch) {
+        stage(ch);
+        if (ch == ch0 + 1) fill_tables(wg, b, parity);
+        wide_barrier<true>();
+      }
+      // The last chunk is being multiplied: start on the next tile.
+      id += nwg;
+      const bool more = id < ntiles;
+      if (more) {
+        wg = tile_of(id);
+        b = decode_brick(a, wg.brick);
+        split_range(a, wg.split, ch0, ch1);
+        aim(b);
+        stage(ch0);
+      }
+      if constexpr (WK > 1) {   // the epilogue's barriers
+        wide_barrier<false>();
+        if constexpr (FM == 2) {
+          wide_barrier<false>();
+          wide_barrier<false>();
+        }
+      }
+      if (!more) break;
+      parity ^= 1;
+    }
+    return;
+  }
+
+  // ---- compute waves ----
+  const int h = lane >> 5;
+  const int wm = wave / WK, kpart = wave % WK;
+  const int sc_full = a.ks * a.c16;
+  const int sc_last = a.ks * (a.c16_total - (a.nchunks - 1) * a.c16);
+  const int n_full = (sc_full - kpart + WK - 1) / WK, n_last = (sc_last - kpart + WK - 1) / WK;
+  // Weight stream: steps kpart, kpart + WK, ... of each chunk, read at a
+  // scalar offset from the section's start.  a_left counts the steps to the
+  // next chunk, where the offset advances by a_jump more (WK need not divide
+  // a chunk's steps).  Past the section's end the loads return zeros, which
+  // are never used.
+  const __amdgpu_buffer_rsrc_t ares =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.a), 0, a.a_bytes, 0x00020000);
+  const uint32_t lane16 = static_cast<uint32_t>(lane) * 16u;
+  const uint32_t a_jump = static_cast<uint32_t>(sc_full - n_full * WK) * 1024u;
+  uint32_t a_off[FM];
+  int a_left = n_full;
+  V8 ra[DA][FM], rb[2][FN];
+  auto fetch_a = [&](int slot, int i) {
+    ra[slot][i] = __builtin_bit_cast(V8, __builtin_amdgcn_raw_buffer_load_b128(ares, lane16, a_off[i], 0));
+  };
+  auto next_a = [&]() {
+    const uint32_t adv = WK * 1024u + (a_left == 1 ? a_jump : 0u);
+    a_left = a_left == 1 ? n_full : a_left - 1;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) a_off[i] += adv;
+  };
+  int ch0, ch1;
+  bool active;
+  // Aims the weight stream at a tile and fills the ring but its last slot
+  // (refilled during the tile's first step).
+  auto start_tile = [&](const Wg &wg) __attribute__((always_inline)) {
+    const int wt = wg.tg * WM + wm;
+    active = wt < a.wave_tiles;
+    split_range(a, wg.split, ch0, ch1);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+      a_off[i] = (static_cast<uint32_t>((active ? wt : 0) * FM + i) * a.stot + ch0 * sc_full + kpart) * 1024u;
+    a_left = n_full;
+#pragma unroll
+    for (int d = 0; d < DA - 1; ++d) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i) fetch_a(d, i);
+      next_a();
+    }
+  };
+  int id = static_cast<int>(blockIdx.x), parity = 0;
+  Wg wg = tile_of(id);
+  start_tile(wg);
+
+  // LDS byte offset of this lane's voxel in each fragment (slots past the
+  // brick read row 0; slots outside the output read rows of the halo: neither
+  // is stored).
+  int vb[FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j) {
+    const int s = 32 * j + lane_slot(lane & 31);
+    const DivMod x = divmod(s, a.bh * a.bw), y = divmod(x.r, a.bw);
+    const int r = (x.q * a.st) * a.hpp + (y.q * a.sh) * a.hwp + y.r * a.sw;
+    vb[j] = (x.q < a.bt ? r : 0) * a.row + 16 * h;
+  }
+  // Step offsets of a chunk, one step per lane (at most 128 steps a part):
+  // part k walks steps k, k + WK, ... of the position-major list.  The last
+  // chunk may hold fewer channels.
+  int tv[2], tl[2], tc[2];
+  {
+    const int c16_last = a.c16_total - (a.nchunks - 1) * a.c16;
+    auto entry = [&](int i, int c16) {
+      const DivMod s = divmod(kpart + i * WK, c16);
+      const DivMod pt = divmod(s.q, a.kh * a.kw), ph = divmod(pt.r, a.kw);
+      return s.q < a.ks ? (pt.q * a.hpp + ph.q * a.hwp + ph.r) * a.row + s.r * 32 : 0;
+    };
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      tv[k] = k == 0 || n_full > 64 ? entry(lane + 64 * k, a.c16) : 0;
+      tl[k] = c16_last == a.c16 ? tv[k] : entry(lane + 64 * k, c16_last);
+      tc[k] = tv[k];
+    }
+  }
+  f32x16 acc[FM][FN];
+  int ch = 0, n = 0, li = 0, buf_off = buf_bytes;   // next chunk, steps of this one, step, buffer
+  // Meets the other waves until a chunk with steps of this part is staged
+  // (or none is left).
+  auto next_chunk = [&]() {
+    li = 0;
+    n = 0x40000000;
+    while (ch < ch1) {
+      wide_barrier<false>();
+      buf_off = buf_off == 0 ? buf_bytes : 0;
+      const bool last = ch == a.nchunks - 1;
+      tc[0] = last ? tl[0] : tv[0];
+      tc[1] = last ? tl[1] : tv[1];
+      ++ch;
+      const int m = last ? n_last : n_full;
+      if (active && m > 0) {
+        n = m;
+        break;
+      }
+    }
+  };
+  auto step_off = [&](int i) {
+    const int lo = __builtin_amdgcn_readlane(tc[0], i & 63), hi = __builtin_amdgcn_readlane(tc[1], i & 63);
+    return (i & 64 ? hi : lo) + buf_off;
+  };
+  auto load_b = [&](int slot, int j, int off) {
+    rb[slot][j] = *reinterpret_cast<const V8 *>(lds + (vb[j] + off));
+  };
+  auto mma = [&](int i, int j, int as, int bs) {
+    if constexpr (std::is_same_v<T, __bf16>)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ra[as][i], rb[bs][j], acc[i][j], 0, 0, 0);
+    else
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ra[as][i], rb[bs][j], acc[i][j], 0, 0, 0);
+  };
+  int off_next = 0;
+  // One step: multiply while the next step's voxels are read (at a chunk's
+  // last step from any offset in range: read again after the barrier) and the
+  // weight slot of the step before is refilled.  One memory instruction goes
+  // between two MFMAs (four waves issuing their reads together would each
+  // wait for the LDS and the vector-memory path to take them all), and the
+  // scalar work of the next step hides behind the last of them.
+  auto step = [&](auto dc, bool refill) __attribute__((always_inline)) {
+    constexpr int D = decltype(dc)::value, PREV = (D + DA - 1) % DA;
+    const int off = off_next;
+    static_for<FN>([&](auto jc) {
+      constexpr int J = decltype(jc)::value;
+      mma(0, J, D, D & 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (J < FN / 2) {
+        load_b((D + 1) & 1, 2 * J, off);
+        load_b((D + 1) & 1, 2 * J + 1, off);
+      }
+      if constexpr (FM == 2) mma(1, J, D, D & 1);
+      if constexpr (J >= FN / 2 && J - FN / 2 < FM) {
+        if (refill) fetch_a(PREV, J - FN / 2);
+      }
+      if constexpr (J == FN / 2) off_next = step_off(li + 2);
+      if constexpr (J == FN - 1) {
+        if (refill) next_a();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if (__builtin_expect(++li == n, 0)) {
+      next_chunk();
+      const int o2 = step_off(0);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) load_b((D + 1) & 1, j, o2);
+      off_next = step_off(1);
+    }
+  };
+  // Epilogue of one tile, 32 filters of every wave tile at a time.  The waves
+  // write their sums to LDS [wave][slot][filter]; then each thread owns four
+  // filters of its wave tile and walks (pooled) voxels, adding the WK parts in
+  // order.  With WK = 1 a wave reads back only what it wrote itself.
+  auto store_pass = [&](const Wg &wg, const Brick &b, int f) __attribute__((always_inline)) {
+    constexpr int STEP = 8 * WK;
+    constexpr int BATCH = 8 / WK;   // slots in flight per thread (eight LDS reads)
+    const int c4 = lane & 7, p0 = kpart * 8 + (lane >> 3);
+    const int2 *outtab = tables + parity * TAB;
+    const uint8_t *col = tile_lds + wm * (WK * SLOTS * TROW) + c4 * 16;
+    const int m_wg = (wm * FM + f) * 32 + c4 * 4;   // within the workgroup
+    const int m0 = wg.tg * MWG + m_wg;
+    const bool live = m0 < a.c_out;
+    auto total = [&](int slot) {
+      float4 s = *reinterpret_cast<const float4 *>(col + slot * TROW);
+#pragma unroll
+      for (int k = 1; k < WK; ++k)
+        s = add4(s, *reinterpret_cast<const float4 *>(col + k * (SLOTS * TROW) + slot * TROW));
+      return s;
+    };
+    if (a.splits > 1) {
+      float *ws = a.ws + static_cast<long>(wg.split) * a.total_vox * a.c_out4 + m0;
+      for (int q = 0; q < SLOTS; q += BATCH * STEP) {   // (uniform trip count)
+        const int p = q + p0;
+        int2 o[BATCH];
+        float4 v[BATCH];
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) o[k] = outtab[p + k * STEP];
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) v[k] = total(o[k].y);
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k)
+          if (live && o[k].x >= 0) *reinterpret_cast<float4 *>(ws + static_cast<long>(o[k].x) * a.c_out4) = v[k];
+      }
+      return;
+    }
+    const float4 bb = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(outtab + SLOTS) + m_wg);
+    if (a.qt * a.qh * a.qw == 1) {
+      const bool quads = (a.c_out & 3) == 0;
+      for (int q = 0; q < SLOTS; q += BATCH * STEP) {   // (uniform trip count)
+        const int p = q + p0;
+        int2 o[BATCH];
+        float4 v[BATCH];
+        union { uint2 u; T e[4]; } r[BATCH];
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+          o[k] = outtab[p + k * STEP];
+          r[k].u = make_uint2(0, 0);
+        }
+        if (a.res && quads) {
+#pragma unroll
+          for (int k = 0; k < BATCH; ++k)
+            if (live && o[k].x >= 0)
+              r[k].u = *reinterpret_cast<const uint2 *>(static_cast<const T *>(a.res) + static_cast<long>(o[k].x) * a.c_out + m0);
+        }
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) v[k] = total(o[k].y);
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+          if (!live || o[k].x < 0) continue;
+          if (quads)   // bias, then the residual (zeros when there is none)
+            put4<T>(a, o[k].x, m0,
+                    activate4<T, false>(a, 0, m0, add4(v[k], bb),
+                                        make_float4(to_f32(r[k].e[0]), to_f32(r[k].e[1]), to_f32(r[k].e[2]), to_f32(r[k].e[3]))));
+          else
+            put4<T>(a, o[k].x, m0, activate4<T>(a, o[k].x, m0, v[k], bb));
+        }
+      }
+      return;
+    }
+    const int np = (a.bt / a.qt) * (a.bh / a.qh) * (a.bw / a.qw);
+    if (a.qt == 2 && a.qh == 2 && a.qw == 2 && !a.res) {
+      for (int q = 0; q < np; q += STEP) {
+        const int p = q + p0;
+        const int2 o = p < np ? outtab[p] : make_int2(-1, 0);
+        float4 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = total(o.y + ((k >> 2) * a.bh + ((k >> 1) & 1)) * a.bw + (k & 1));
+        float4 best = activate4<T, false>(a, 0, m0, v[0], bb);
+#pragma unroll
+        for (int k = 1; k < 8; ++k) best = max4(best, activate4<T, false>(a, 0, m0, v[k], bb));
+        if (live && o.x >= 0) put4<T>(a, o.x, m0, best);
+      }
+      return;
+    }
+    for (int q = 0; q < np; q += STEP) {
+      const int p = q + p0;
+      const int2 o = p < np ? outtab[p] : make_int2(-1, 0);
+      if (!live || o.x < 0) continue;
+      float4 best = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int dt = 0; dt < a.qt; ++dt)
+        for (int dh = 0; dh < a.qh; ++dh)
+          for (int dw = 0; dw < a.qw; ++dw) {
+            const int s = o.y + (dt * a.bh + dh) * a.bw + dw;
+            long vox = 0;
+            if (a.res) {
+              const DivMod x = divmod(s, a.bh * a.bw), y = divmod(x.r, a.bw);
+              vox = ((static_cast<long>(b.nb) * a.to + b.ot0 + x.q) * a.ho + b.oh0 + y.q) * a.wo + b.ow0 + y.r;
+            }
+            const float4 v = activate4<T>(a, vox, m0, total(s), bb);
+            best = (dt | dh | dw) ? max4(best, v) : v;
+          }
+      put4<T>(a, o.x, m0, best);
+    }
+  };
+  for (;;) {
+    const int total_steps =
+        active ? (ch1 - ch0) * n_full - (ch1 == a.nchunks ? n_full - n_last : 0) : 0;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    ch = ch0;
+    next_chunk();
+    {
+      const int off = step_off(0);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) load_b(0, j, off);
+      off_next = step_off(1);
+    }
+    int t = 0;
+    for (; t + DA <= total_steps; t += DA) static_for<DA>([&](auto dc) { step(dc, true); });
+    const int rem = total_steps - t;
+    static_for<DA - 1>([&](auto dc) {
+      if (decltype(dc)::value < rem) step(dc, false);
+    });
+    // (idle waves have met every chunk's barrier in next_chunk)
+    const Wg done = wg;
+    id += nwg;
+    const Brick b = decode_brick(a, done.brick);
+    uint8_t *tile = tile_lds + wave * (SLOTS * TROW) + 16 * h + lane_slot(lane & 31) * TROW;
+    auto put_sums = [&](auto fc) __attribute__((always_inline)) {
+      constexpr int F = decltype(fc)::value;
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<f32x4 *>(tile + 32 * j * TROW + q * 32) =
+              f32x4{acc[F][j][4 * q], acc[F][j][4 * q + 1], acc[F][j][4 * q + 2], acc[F][j][4 * q + 3]};
+    };
+    auto meet = [] {   // the waves that share a tile (one wave alone: its own writes)
+      if constexpr (WK > 1) wide_barrier<false>();
+      else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+    static_for<FM>([&](auto fc) {
+      if (decltype(fc)::value) meet();
+      put_sums(fc);
+      meet();
+      store_pass(done, b, decltype(fc)::value);
+    });
+    if (id >= ntiles) break;
+    wg = tile_of(id);
+    start_tile(wg);
+    parity ^= 1;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2199,6 +2728,35 @@ int launch_items16(const ConvArgs &a, int dtype, int mfw, int map, void *stream)
     if (mfw == 4) RT3D_ITEMS16(_Float16, 4);
   }
 #undef RT3D_ITEMS16
+  return hipErrorInvalidValue;
+}
+
+template <typename K>
+int launch_wide_kernel(K kernel, const WideArgs &a, void *stream) {
+  const hipError_t e = prepare(kernel);
+  if (e != hipSuccess) return e;
+  if (a.grid <= 0) return hipSuccess;
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(a.grid)), dim3(512),
+                     static_cast<size_t>(a.lds_bytes), static_cast<hipStream_t>(stream), a);
+  return hipGetLastError();
+}
+
+int launch_wide16(const WideArgs &a, int dtype, int fm, int wk, void *stream) {
+#define RT3D_WIDE_FM(T, FM)                                                              \
+  do {                                                                                   \
+    if (wk == 1) return launch_wide_kernel(wide_kernel<T, FM, 4, 1>, a, stream);         \
+    if (wk == 2) return launch_wide_kernel(wide_kernel<T, FM, 4, 2>, a, stream);         \
+    if (wk == 4) return launch_wide_kernel(wide_kernel<T, FM, 4, 4>, a, stream);         \
+  } while (0)
+#define RT3D_WIDE(T)                                                                     \
+  do {                                                                                   \
+    if (fm == 1) RT3D_WIDE_FM(T, 1);                                                     \
+    if (fm == 2) RT3D_WIDE_FM(T, 2);                                                     \
+  } while (0)
+  if (dtype == RT3D_BF16) RT3D_WIDE(__bf16);
+  else if (dtype == RT3D_F16) RT3D_WIDE(_Float16);
+#undef RT3D_WIDE
+#undef RT3D_WIDE_FM
   return hipErrorInvalidValue;
 }
 
