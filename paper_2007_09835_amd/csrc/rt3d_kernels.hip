@@ -2295,6 +2295,78 @@ __global__ __launch_bounds__(256) void maxpool_kernel(const T *__restrict__ x, T
   *reinterpret_cast<Vec *>(y + static_cast<long>(vox) * p.c + cb * VEC) = o.u;
 }
 
+// Windows of three along w: one thread computes R outputs along w and walks
+// the input columns they span.  A column's maximum over (t, h) is shared by
+// the windows that hold it, so an output costs (R - 1 + 3 / SW) KT KH SW / R
+// loads and compares instead of 3 KT KH (the 3x3x3 stride-1 pool was bound by
+// its vector ALU work: 27 loads of 8 elements, each converted, compared and
+// selected; S3D m3c at batch 4, 4x8x28x28x256: 43.5 -> 17.2 us).  Positions
+// outside the input are clamped to the border voxel, which lies in the same
+// window (padding is at most half the window), so no load is conditional.
+// NaN as in maxpool_kernel: a window's first voxel decides, others are
+// skipped.
+template <typename T, int VEC, int KT, int KH, int SW, int R>
+__global__ __launch_bounds__(256) void maxpool_run_kernel(const T *__restrict__ x, T *__restrict__ y,
+                                                          PoolArgs p) {
+  const int item = static_cast<int>(blockIdx.x) * 256 + static_cast<int>(threadIdx.x);
+  if (item >= p.items) return;
+  const int runs = (p.wo + R - 1) / R;
+  const DivMod vc = divmod(item, p.cv);
+  const int vox = vc.q + p.item0 / p.cv;    // item0 is a multiple of cv
+  const DivMod a = divmod(vox, runs), b = divmod(a.q, p.ho), d = divmod(b.q, p.to);
+  const int ow0 = a.r * R, oh = b.r, ot = d.r, nb = d.q;
+  using Vec = std::conditional_t<VEC * sizeof(T) == 16, uint4, T>;
+  union Pack { Vec u; T e[VEC]; };
+  long row[KT][KH];                         // element offset of each (t, h) line of the window
+#pragma unroll
+  for (int it = 0; it < KT; ++it)
+#pragma unroll
+    for (int ih = 0; ih < KH; ++ih) {
+      const int zt = min(max(ot * p.st - p.pt + it, 0), p.t - 1), zh = min(max(oh * p.sh - p.ph + ih, 0), p.h - 1);
+      row[it][ih] = (((static_cast<long>(nb) * p.t + zt) * p.h + zh) * p.w) * p.c + vc.r * VEC;
+    }
+  T *out = y + ((static_cast<long>(nb) * p.to + ot) * p.ho + oh) * static_cast<long>(p.wo) * p.c + vc.r * VEC;
+  float col[3][VEC];                        // maxima of the last three columns
+  Pack first[3];                            // their voxels at the window's first (t, h)
+  constexpr int COLS = (R - 1) * SW + 3;
+#pragma unroll
+  for (int cx = 0; cx < COLS; ++cx) {
+    const long zw = static_cast<long>(min(max(ow0 * SW - p.pw + cx, 0), p.w - 1)) * p.c;
+    Pack v[KT][KH];
+#pragma unroll
+    for (int it = 0; it < KT; ++it)
+#pragma unroll
+      for (int ih = 0; ih < KH; ++ih) v[it][ih].u = *reinterpret_cast<const Vec *>(x + row[it][ih] + zw);
+    first[cx % 3] = v[0][0];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      float m = -__builtin_inff();
+#pragma unroll
+      for (int it = 0; it < KT; ++it)
+#pragma unroll
+        for (int ih = 0; ih < KH; ++ih) {
+          const float f = static_cast<float>(v[it][ih].e[e]);
+          m = f > m ? f : m;
+        }
+      col[cx % 3][e] = m;
+    }
+    if (cx >= 2 && (cx - 2) % SW == 0) {
+      const int r = (cx - 2) / SW;          // (a constant in the unrolled loop)
+      if (ow0 + r < p.wo) {
+        Pack o;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          const float f0 = static_cast<float>(first[(cx - 2) % 3].e[e]);
+          float m = col[0][e] > col[1][e] ? col[0][e] : col[1][e];
+          m = col[2][e] > m ? col[2][e] : m;
+          o.e[e] = f0 != f0 ? first[(cx - 2) % 3].e[e] : static_cast<T>(m);
+        }
+        *reinterpret_cast<Vec *>(out + static_cast<long>(ow0 + r) * p.c) = o.u;
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Group norms and the reweighted group-lasso penalty (Section 4).
 // A "unit" is what one norm covers: one kernel position of one kernel group
@@ -2796,6 +2868,33 @@ int launch_kgs_exact_f32(const ConvArgs &a, void *stream) {
   return launch_conv(kgs_exact_f32_kernel<2>, a, stream);
 }
 
+// Outputs per thread of maxpool_run_kernel for this pool, 0 when it does not
+// apply (windows other than 3x3x3 and 1x3x3, strides other than 1 or 2 along
+// w).  Seven along w where that still gives each SIMD four waves, four where
+// that gives it one; smaller pools are bound by latency and keep a thread per
+// output (S3D m5, 2x7x7x832 at batch 1).
+int pool_run(const PoolArgs &p, long outs) {
+  if (!((p.kt == 3 || p.kt == 1) && p.kh == 3 && p.kw == 3 && (p.sw == 1 || p.sw == 2))) return 0;
+  const long lines = outs / p.wo * p.cv;
+  for (const int r : {7, 4})
+    if (lines * ((p.wo + r - 1) / r) >= (r == 7 ? 262144 : 65536)) return r;
+  return 0;
+}
+
+template <typename T, int VEC, int R>
+void pool_run_launch(dim3 grid, hipStream_t s, const void *x, void *y, const PoolArgs &p) {
+  const T *xs = static_cast<const T *>(x);
+  T *ys = static_cast<T *>(y);
+  if (p.kt == 3 && p.sw == 1)
+    hipLaunchKernelGGL((maxpool_run_kernel<T, VEC, 3, 3, 1, R>), grid, dim3(256), 0, s, xs, ys, p);
+  else if (p.kt == 3)
+    hipLaunchKernelGGL((maxpool_run_kernel<T, VEC, 3, 3, 2, R>), grid, dim3(256), 0, s, xs, ys, p);
+  else if (p.sw == 1)
+    hipLaunchKernelGGL((maxpool_run_kernel<T, VEC, 1, 3, 1, R>), grid, dim3(256), 0, s, xs, ys, p);
+  else
+    hipLaunchKernelGGL((maxpool_run_kernel<T, VEC, 1, 3, 2, R>), grid, dim3(256), 0, s, xs, ys, p);
+}
+
 // The windows of the C3D and S3D stacks get unrolled kernels.
 template <typename T, int VEC>
 void pool_launch(dim3 grid, hipStream_t s, const void *x, void *y, const PoolArgs &p) {
@@ -2822,24 +2921,27 @@ int launch_maxpool(int n, int c, int t, int h, int w, int kt, int kh, int kw, in
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int vec = dtype == RT3D_F32 ? (c % 4 == 0 ? 4 : 1) : (c % 8 == 0 ? 8 : 1);
   PoolArgs p{n, c, t, h, w, kt, kh, kw, st, sh, sw, pt, ph, pw, to, ho, wo, c / vec, 0, 0};
-  // Launches of whole voxels with fewer than 2^24 items each (the fast
-  // divide in the kernel needs that).
+  // Launches of whole voxels (runs of voxels) with fewer than 2^24 items each
+  // (the fast divide in the kernels needs that).
+  const int run = vec > 1 ? pool_run(p, outs) : 0;
+  const long voxels = run ? outs / wo * ((wo + run - 1) / run) : outs;
   const long per_launch = ((1l << 24) - 1) / p.cv * p.cv;
-  const long total = outs * p.cv;
+  const long total = voxels * p.cv;
   for (long first = 0; first < total; first += per_launch) {
     p.item0 = static_cast<int>(first);
     p.items = static_cast<int>(std::min(per_launch, total - first));
     const dim3 grid(static_cast<unsigned>((p.items + 255) / 256));
-    if (dtype == RT3D_F32) {
-      if (vec == 4) pool_launch<float, 4>(grid, s, x, y, p);
-      else pool_launch<float, 1>(grid, s, x, y, p);
-    } else if (dtype == RT3D_BF16) {
-      if (vec == 8) pool_launch<__bf16, 8>(grid, s, x, y, p);
-      else pool_launch<__bf16, 1>(grid, s, x, y, p);
-    } else {
-      if (vec == 8) pool_launch<_Float16, 8>(grid, s, x, y, p);
-      else pool_launch<_Float16, 1>(grid, s, x, y, p);
-    }
+#define RT3D_POOL(T, V)                                                \
+  do {                                                                 \
+    if (vec == V && run == 7) pool_run_launch<T, V, 7>(grid, s, x, y, p);      \
+    else if (vec == V && run == 4) pool_run_launch<T, V, 4>(grid, s, x, y, p); \
+    else if (vec == V) pool_launch<T, V>(grid, s, x, y, p);            \
+    else pool_launch<T, 1>(grid, s, x, y, p);                          \
+  } while (0)
+    if (dtype == RT3D_F32) RT3D_POOL(float, 4);
+    else if (dtype == RT3D_BF16) RT3D_POOL(__bf16, 8);
+    else RT3D_POOL(_Float16, 8);
+#undef RT3D_POOL
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
