@@ -1440,6 +1440,43 @@ WidePlan wide_tiling(const Geom &g, int fn) {
   return best;
 }
 
+// RGB kernel: halo extent and pitches of a 4x4x32 brick, K-steps, LDS bytes.
+struct RgbShape {
+  int ht, hh, hwp, hpp, steps, lds;
+  bool ok;
+};
+
+RgbShape rgb_shape(const Geom &g) {
+  RgbShape r{};
+  r.ht = 3 * g.st + g.kt;
+  r.hh = 3 * g.sh + g.kh;
+  r.hwp = 31 * g.sw + (g.kw + 3) / 4 * 4;   // the last tap group may read past the kernel
+  r.hpp = r.hh * r.hwp;
+  r.steps = g.kt * g.kh * ((g.kw + 3) / 4);
+  r.lds = 2 * r.ht * r.hpp * 8 + r.steps * 2048 + 256;
+  r.ok = r.ht * r.hpp <= 16 * 256 && r.steps <= 64 && r.lds <= kWideLds;
+  return r;
+}
+
+// The RGB kernel's weights: step (kernel row, tap group s), lane (m, half),
+// element e = channel e % 4 of tap 4 s + 2 half + e / 4.
+void build_rgb_layout(const Geom &g, const uint8_t *w, const Mask4 *m4, std::vector<uint8_t> &out) {
+  const RgbShape r = rgb_shape(g);
+  const int tiles = (g.c_out + 63) / 64, s4 = (g.kw + 3) / 4;
+  out.assign(static_cast<size_t>(tiles) * r.steps * 2048, 0);
+  const uint16_t *src = reinterpret_cast<const uint16_t *>(w);
+  uint16_t *dst = reinterpret_cast<uint16_t *>(out.data());
+  for (int m = 0; m < g.c_out; ++m)
+    for (int c = 0; c < g.c_in; ++c)
+      for (int pos = 0; pos < g.ks; ++pos) {
+        if (m4 && !m4->kept(m / 4, 0, pos)) continue;
+        const int iw = pos % g.kw, row = pos / g.kw, step = row * s4 + iw / 4, tap = iw % 4;
+        const size_t frag = (static_cast<size_t>(m / 64) * r.steps + step) * 2 + (m % 64) / 32;
+        dst[frag * 512 + ((m & 31) + 32 * (tap >> 1)) * 8 + (tap & 1) * 4 + c] =
+            src[(static_cast<size_t>(m) * g.c_in + c) * g.ks + pos];
+      }
+}
+
 // Does a pack write the wide layout?  16-bit layers off the small-channel
 // kernel, unless a tuning switch names an item-kernel layout.
 bool wide_wanted(const Geom &g, bool small, const Mask4 *m4) {
@@ -1651,6 +1688,13 @@ int pair_width(const Geom &g, const Mask4 *m4) {
 
 // Adds the wide layout where the planner wants one.
 void add_wide(const Geom &g, bool small, const uint8_t *w, const Mask4 *m4, Layout &L) {
+  if (small) {
+    // (not where a tuning switch asks for a layout of the small-channel kernel)
+    if (tune("wide") == 0 || tune("small_mfw") >= 0 || !rgb_shape(g).ok) return;
+    build_rgb_layout(g, w, m4, L.wide_a);
+    L.wide.rgb = 1;
+    return;
+  }
   if (!wide_wanted(g, small, m4)) return;
   L.wide = wide_tiling(g, 4);
   if (L.wide.c16 > 0 && (g.c_in + 15) / 16 / L.wide.c16 < 4000) build_wide_layout(g, L.wide, w, m4, L.wide_a);
@@ -1893,7 +1937,7 @@ WidePlan wide_plan_of(const rt3d_pack_info *info) {
 WideLaunch plan_wide(const rt3d_conv3d_desc *d, const WidePlan &wp, uint64_t ws_cap,
                      double item_cycles) {
   WideLaunch none;
-  if (wp.a_off == 0) return none;
+  if (wp.a_off == 0 || wp.rgb) return none;
   const int x_pitch = d->x_c_total != 0 ? d->x_c_total : d->c_in;
   if (x_pitch % 8 != 0 || d->x_c_off % 8 != 0) return none;
   const Geom g = geom_of(d);
@@ -1994,6 +2038,33 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   if (static_cast<long>(a.n) * a.nbt * a.nbh * a.nbw * a.ntg * a.splits >= (1L << 24))
     return fail(RT3D_ERR_UNSUPPORTED, "layer needs 2^24 or more workgroups");
   int e;
+  // Layers with up to 4 input channels: the RGB kernel, except where a
+  // residual is added or an output voxel's filters are not whole 16-byte
+  // words (the small-channel kernel).
+  if (wp.a_off != 0 && wp.rgb && !residual && tune("wide") != 0 && (g.c_out | a.y_pitch | a.y_off) % 8 == 0) {
+    const RgbShape r = rgb_shape(g);
+    WideArgs ra{};
+    static_cast<ConvArgs &>(ra) = a;
+    ra.a = b + wp.a_off;
+    ra.bt = 4; ra.bh = 4; ra.bw = 32;
+    ra.nbt = (g.to + 3) / 4;
+    ra.nbh = (g.ho + 3) / 4;
+    ra.nbw = (g.wo + 31) / 32;
+    ra.ht = r.ht; ra.hh = r.hh; ra.hw = r.hwp; ra.hwp = r.hwp; ra.hpp = r.hpp;
+    ra.kh = g.kh; ra.kw = g.kw; ra.ks = g.ks;
+    ra.stot = r.steps;
+    ra.buf_bytes = r.ht * r.hpp * 8;
+    ra.lds_bytes = r.lds;
+    ra.ntg = (g.c_out + 63) / 64;
+    ra.nbricks = static_cast<int32_t>(static_cast<long>(g.n) * ra.nbt * ra.nbh * ra.nbw);
+    // one workgroup per CU, a multiple of the filter tiles
+    const long cus = std::max<long>(1, device_cus() / ra.ntg);
+    ra.grid = static_cast<int32_t>(std::min<long>(cus, ra.nbricks) * ra.ntg);
+    e = launch_rgb16(ra, d->dtype, stream);
+    if (e != hipSuccess)
+      return fail(RT3D_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(static_cast<hipError_t>(e)));
+    return ok();
+  }
   if (wl.fm > 0) {
     WideArgs wa{};
     static_cast<ConvArgs &>(wa) = a;

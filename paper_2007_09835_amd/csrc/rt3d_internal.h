@@ -115,7 +115,10 @@ struct WidePlan {
   uint8_t c16;             // 16-channel slices per chunk
   uint16_t hwp, hpp;       // halo pitches in voxels: per row of w, per plane of (h, w)
   uint8_t fn;              // 32-slot voxel fragments per brick
-  uint8_t reserved[7];
+  uint8_t rgb;             // 1: the RGB kernel's weights instead (c_in <= 4): [64 filters][step]
+                           // [32-filter row][lane][8], steps over kernel rows and groups of four
+                           // w taps; bricks are 4x4x32, the geometry fields are unused
+  uint8_t reserved[6];
 };
 static_assert(sizeof(Plan) + sizeof(WidePlan) <= sizeof(((rt3d_pack_info *)0)->plan),
               "plans do not fit");
@@ -176,6 +179,7 @@ void *noalloc_scratch();
 // with `lds` bytes of dynamic LDS each; 0 when the runtime cannot say.
 int conv_resident(int variant, int dtype, int mfw, int nf, size_t lds);
 int launch_items16(const ConvArgs &a, int dtype, int mfw, int map, void *stream);
+int launch_rgb16(const WideArgs &a, int dtype, void *stream);
 int launch_wide16(const WideArgs &a, int dtype, int fm, int wk, void *stream);
 int launch_small16(const ConvArgs &a, int dtype, int mfw, void *stream);
 size_t small_lds_bytes(const ConvArgs &a);

@@ -100,8 +100,8 @@ def test_wide_layout_decodes_to_masked_weights(dt, case, monkeypatch):
 
 
 def test_wide_layout_is_left_out(monkeypatch):
-    """fp32, the small-channel kernel, fewer than 16 input channels and a
-    tuning switch that names an item-kernel layout keep a blob without it."""
+    """fp32, 5 to 15 input channels and a tuning switch that names an
+    item-kernel layout keep a blob without it."""
     def a_off(c_in, dt, tune=None, thw=(4, 8, 8)):
         if tune:
             monkeypatch.setenv("RT3D_TUNE", tune)
@@ -113,6 +113,7 @@ def test_wide_layout_is_left_out(monkeypatch):
     assert a_off(32, "bf16") > 0
     assert a_off(32, "f32") == 0
     assert a_off(12, "bf16") == 0
-    assert a_off(3, "bf16", thw=(4, 8, 44)) == 0
+    assert a_off(3, "bf16", thw=(4, 8, 44)) > 0       # the RGB kernel's weights
+    assert a_off(3, "bf16", "small_mfw=1", thw=(4, 8, 44)) == 0
     for tune in ("wide=0", "slots=64", "dense_mfw=1", "cc=32"):
         assert a_off(32, "bf16", tune) == 0
