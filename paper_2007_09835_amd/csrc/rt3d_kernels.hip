@@ -2803,6 +2803,112 @@ __global__ __launch_bounds__(256) void group_reweight_kernel(GroupArgs a) {
   }
 }
 
+// KGS scope with GM x 4 groups: one thread per unit keeps its GM x 4 weights in
+// registers from the only load to the last store.  The staged kernel above is
+// bound by latency, not by HBM: a barrier parts its loads from its stores and
+// every element costs two divisions to find its unit.  Here all of a thread's
+// loads are in flight together, a unit is found by one division and nothing
+// waits for another wave until the penalty sum.  Lanes of neighbouring positions
+// read neighbouring addresses (runs of ks elements); the four channels of a unit
+// together use every byte of the lines they touch.  Sums run in the staged
+// kernel's order, so every output is the same bit for bit.  A thread reads its
+// own elements before it writes them: the proximal output may overwrite the
+// weights in place.
+// With the penalty sum's launch, staged -> here: 512x512x27 in groups of 4
+// filters, proximal output, f32 21.1 -> 18.2 us (3.4 TB/s), bf16 23.2 -> 15.3; of 8
+// filters f32 23.6 -> 15.2, of 16 33.9 -> 16.5; 256x512x3 f32 13.1 -> 8.9; 40x24x27
+// 7.4 -> 6.3.
+template <typename T, int NORM, int GM>
+__global__ __launch_bounds__(256) void group_reweight_unit_kernel(GroupArgs a) {
+  constexpr int GN = 4;
+  __shared__ float red[256];
+  const int tid = static_cast<int>(threadIdx.x), nt = static_cast<int>(blockDim.x);
+  const int blk = static_cast<int>(blockIdx.x);
+  const int p = blk / a.nqc, qc = blk - p * a.nqc;
+  const int m0 = p * GM, gme = min(GM, a.M - m0);
+  const int q0 = qc * a.qb, nq = min(a.qb, a.Q - q0);
+  const int pitch = a.N * a.ks;  // elements between filter rows (the tensor has < 2^31)
+
+  float local = 0.f;  // this thread's share of sum(pen * norm)
+  for (int u = tid; u < nq * a.ks; u += nt) {
+    const DivMod d = divmod(u, a.ks);
+    const int c0 = (q0 + d.q) * GN, gne = min(GN, a.N - c0);
+    const long base = static_cast<long>(m0) * pitch + static_cast<long>(c0) * a.ks + d.r;
+    const T *src = static_cast<const T *>(a.w) + base;
+    T raw[GM][GN];  // rows and channels past the edge repeat the last one
+#pragma unroll
+    for (int i = 0; i < GM; ++i)
+#pragma unroll
+      for (int j = 0; j < GN; ++j)
+        raw[i][j] = src[static_cast<long>(min(i, gme - 1)) * pitch + min(j, gne - 1) * a.ks];
+    const long gu = (static_cast<long>(p) * a.Q + q0 + d.q) * a.ks + d.r;
+    const float pu = a.pen ? a.pen[gu] : 1.f;
+    float acc = 0.f;
+#pragma unroll
+    for (int i = 0; i < GM; ++i)
+#pragma unroll
+      for (int j = 0; j < GN; ++j)
+        acc = i < gme && j < gne ? acc + norm_term<NORM>(to_f32(raw[i][j])) : acc;
+    const float n = NORM == 2 ? sqrtf(acc) : acc;
+    local += pu * n;
+    if (a.norms) a.norms[gu] = n;
+    if (a.pen_next) a.pen_next[gu] = 1.f / (n * n + a.eps);
+    if (a.mask) a.mask[gu] = n > a.tau ? 1 : 0;
+    const float lp = a.lambda * pu, theta = a.step * lp;
+    const float f = NORM == 2 && n > 0.f ? 1.f - theta / n : 0.f;
+    if (a.grad) {
+      float *gp = a.grad + base;
+#pragma unroll
+      for (int i0 = 0; i0 < GM; i0 += 4) {
+        float g0[4][GN];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < GN; ++j)
+            g0[r][j] = gp[static_cast<long>(min(i0 + r, gme - 1)) * pitch + min(j, gne - 1) * a.ks];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < GN; ++j) {
+            if (i0 + r >= gme || j >= gne) continue;
+            const float v = to_f32(raw[i0 + r][j]);
+            const float sgn = v > 0.f ? 1.f : (v < 0.f ? -1.f : 0.f);
+            gp[static_cast<long>(i0 + r) * pitch + j * a.ks] =
+                g0[r][j] + (NORM == 2 ? (n > 0.f ? lp * v / n : 0.f) : lp * sgn);
+          }
+      }
+    }
+    if (a.w_prox) {
+      T *dst = static_cast<T *>(a.w_prox) + base;
+#pragma unroll
+      for (int i = 0; i < GM; ++i)
+#pragma unroll
+        for (int j = 0; j < GN; ++j) {
+          if (i >= gme || j >= gne) continue;
+          const float v = to_f32(raw[i][j]);
+          float z;
+          if constexpr (NORM == 2) {
+            z = f > 0.f ? v * f : 0.f;
+          } else {
+            const float sgn = v > 0.f ? 1.f : (v < 0.f ? -1.f : 0.f);
+            const float m = fabsf(v) - theta;
+            z = m > 0.f ? sgn * m : 0.f;
+          }
+          dst[static_cast<long>(i) * pitch + j * a.ks] = static_cast<T>(z);
+        }
+    }
+  }
+
+  if (!a.partial) return;
+  red[tid] = local;
+  __syncthreads();
+  for (int off = nt >> 1; off > 0; off >>= 1) {
+    if (tid < off) red[tid] += red[tid + off];
+    __syncthreads();
+  }
+  if (tid == 0) a.partial[blk] = red[0];
+}
+
 // reg = lambda * the sum of the per-workgroup partial sums, in index order
 // (a second launch: the kernel boundary makes every partial visible).
 __global__ __launch_bounds__(256) void reg_finalize_kernel(const float *partial, int n,
@@ -3222,6 +3328,33 @@ int launch_group_reweight(const GroupArgs &a, int dtype, int norm, int scope, si
                           void *stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   const dim3 grid(static_cast<unsigned>(a.P) * static_cast<unsigned>(a.nqc));
+  // Four-channel groups of 4, 8 or 16 filters (a unit fits the registers) take
+  // the unit kernel, on no more waves than the block's units fill: it was the
+  // faster one at all 14 sizes measured (32x16x3 to 512x512x27, 7.8 -> 6.3 us to
+  // 40.0 -> 21.0).  Other group shapes and the vanilla scope stay staged.
+  if (scope == 0 && a.gn == 4 && (a.gm == 4 || a.gm == 8 || a.gm == 16)) {
+    const int units = a.qb * a.ks;
+    const dim3 threads(units > 128 ? 256 : units > 64 ? 128 : 64);
+#define RT3D_UNIT_GM(T, GM)                                                                   \
+  do {                                                                                        \
+    if (norm == 2)                                                                            \
+      hipLaunchKernelGGL((group_reweight_unit_kernel<T, 2, GM>), grid, threads, 0, s, a);     \
+    else                                                                                      \
+      hipLaunchKernelGGL((group_reweight_unit_kernel<T, 1, GM>), grid, threads, 0, s, a);     \
+  } while (0)
+#define RT3D_UNIT(T)                          \
+  do {                                        \
+    if (a.gm == 4) RT3D_UNIT_GM(T, 4);        \
+    else if (a.gm == 8) RT3D_UNIT_GM(T, 8);   \
+    else RT3D_UNIT_GM(T, 16);                 \
+  } while (0)
+    if (dtype == RT3D_F32) RT3D_UNIT(float);
+    else if (dtype == RT3D_BF16) RT3D_UNIT(__bf16);
+    else RT3D_UNIT(_Float16);
+#undef RT3D_UNIT
+#undef RT3D_UNIT_GM
+    return hipGetLastError();
+  }
 #define RT3D_GROUP(T)                                                                        \
   do {                                                                                       \
     if (norm == 2 && scope == 0)                                                             \
