@@ -2815,7 +2815,7 @@ __global__ __launch_bounds__(256) void group_reweight_kernel(GroupArgs a) {
 // own elements before it writes them: the proximal output may overwrite the
 // weights in place.
 // With the penalty sum's launch, staged -> here: 512x512x27 in groups of 4
-// filters, proximal output, f32 21.1 -> 18.2 us (3.4 TB/s), bf16 23.2 -> 15.3; of 8
+// filters, proximal output, f32 21.1 -> 18.2 us (3.4 TB/s of its bytes), bf16 23.2 -> 15.3; of 8
 // filters f32 23.6 -> 15.2, of 16 33.9 -> 16.5; 256x512x3 f32 13.1 -> 8.9; 40x24x27
 // 7.4 -> 6.3.
 template <typename T, int NORM, int GM>
@@ -2911,12 +2911,22 @@ __global__ __launch_bounds__(256) void group_reweight_unit_kernel(GroupArgs a) {
 
 // reg = lambda * the sum of the per-workgroup partial sums, in index order
 // (a second launch: the kernel boundary makes every partial visible).
+// One workgroup bound by load latency: eight loads per thread go out together
+// (most sums have at most 2048 partials) and are added in the old order.
+// Whole pass, one load at a time -> eight: 512x512x27 f32 prox 18.2 -> 17.3 us,
+// 256x512x3 8.9 -> 7.1.
 __global__ __launch_bounds__(256) void reg_finalize_kernel(const float *partial, int n,
                                                            float lambda, float *reg) {
   __shared__ float red[256];
   const int tid = static_cast<int>(threadIdx.x);
   float s = 0.f;
-  for (int i = tid; i < n; i += 256) s += partial[i];
+  for (int i0 = tid; i0 < n; i0 += 8 * 256) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = partial[min(i0 + 256 * k, n - 1)];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s = i0 + 256 * k < n ? s + v[k] : s;
+  }
   red[tid] = s;
   __syncthreads();
   for (int off = 128; off > 0; off >>= 1) {
