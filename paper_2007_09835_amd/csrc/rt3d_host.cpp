@@ -1307,6 +1307,14 @@ struct WideLaunch {
   double cycles = 0;       // modelled time
 };
 
+// Time model of the wide kernel, in cycles: a K-step, a tile's epilogue (by
+// 32-filter rows per wave), staging per halo row and slice with what the
+// compute waves hide of it, a chunk's barrier, a launch's start, the
+// reduction's start and a partial sum's byte, written and read back.
+constexpr double kWideStep[3] = {0, 223, 349}, kWideTile[3] = {0, 7645, 12850};
+constexpr double kWideLoad = 5.8, kWideLoadFree = 4817, kWideChunk = 670, kWideStart = 4450;
+constexpr double kWideReduceStart = 4700, kWidePartialBytes = 0.63;
+
 // The best launch shape of a wide plan, by a time model in cycles.  A
 // workgroup per CU walks its tiles one after the other; a tile is its chunks
 // (K-steps, or the loads of the next chunk where those take longer, and a
@@ -1326,10 +1334,7 @@ WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cu
   const int rows32 = (g.c_out + 31) / 32;
   const double rows = static_cast<double>((wp.bt - 1) * g.st + g.kt) * ((wp.bh - 1) * g.sh + g.kh) *
                       ((wp.bw - 1) * g.sw + g.kw);
-  constexpr double kStep[3] = {0, 223, 349}, kTile[3] = {0, 7645, 12850};
-  constexpr double kLoad = 5.8, kLoadFree = 4817, kChunk = 670, kStart = 4450;
-  constexpr double kReduceStart = 4700, kPartialBytes = 0.63;   // per byte written and read back
-  const double load = kLoad * rows * wp.c16;
+  const double load = kWideLoad * rows * wp.c16;
   double best_t = -1;
   for (int fm = 1; fm <= 2; ++fm) {
     if (want_fm > 0 && want_fm != fm) continue;
@@ -1341,7 +1346,7 @@ WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cu
       const int chunk_steps = (g.ks * wp.c16 + wk - 1) / wk;
       if (chunk_steps > kWideSteps) continue;
       const long ntg = (tiles + wm - 1) / wm;
-      const double chunk = std::max(chunk_steps * kStep[fm], load - kLoadFree) + kChunk;
+      const double chunk = std::max(chunk_steps * kWideStep[fm], load - kWideLoadFree) + kWideChunk;
       for (int per = nch; per >= 1;) {   // chunks per workgroup; s = ceil(nch / per) splits
         const int s = (nch + per - 1) / per;
         if (s > 1 && per_split * s > ws_cap) break;
@@ -1349,8 +1354,8 @@ WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cu
         const long n = bricks * ntg * s;
         if (n >= (1L << 24)) break;
         if (!want || s <= want) {
-          double t = static_cast<double>((n + cus - 1) / cus) * (per * chunk + kTile[fm]) + kStart + load;
-          if (s > 1) t += kReduceStart + kPartialBytes / 1000 * 2.0 * static_cast<double>(s * per_split);
+          double t = static_cast<double>((n + cus - 1) / cus) * (per * chunk + kWideTile[fm]) + kWideStart + load;
+          if (s > 1) t += kWideReduceStart + kWidePartialBytes / 1000 * 2.0 * static_cast<double>(s * per_split);
           if (best_t < 0 || t < best_t || (want && s > best.splits)) {
             best_t = t;
             best.fm = fm;
@@ -1369,6 +1374,15 @@ WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cu
     }
   }
   return best;
+}
+
+// A lower bound of best_wide's cycles: one tile of one chunk, its reduction
+// cut four ways, after the start and the first loads.
+double least_wide(const Geom &g, const WidePlan &wp) {
+  const double rows = static_cast<double>((wp.bt - 1) * g.st + g.kt) * ((wp.bh - 1) * g.sh + g.kh) *
+                      ((wp.bw - 1) * g.sw + g.kw);
+  return kWideStart + kWideLoad * rows * wp.c16 + kWideChunk + kWideTile[1] +
+         (g.ks * wp.c16 + 3) / 4 * kWideStep[1];
 }
 
 // Brick, halo pitches and chunk width of the wide kernel for this batch
@@ -1942,11 +1956,17 @@ WideLaunch plan_wide(const rt3d_conv3d_desc *d, const WidePlan &wp, uint64_t ws_
   if (x_pitch % 8 != 0 || d->x_c_off % 8 != 0) return none;
   const Geom g = geom_of(d);
   if (static_cast<double>(g.t) * g.h * g.w * x_pitch * 2 >= 4.29e9) return none;
-  WideLaunch L = best_wide(g, wp, std::min<uint64_t>(ws_cap, kScratchBytes), device_cus(),
-                           tune("splits"), tune("wide_fm"), tune("wide_wm"));
-  if (L.fm == 0) return none;
+  const bool tuned = std::getenv("RT3D_TUNE") != nullptr;   // (one look at the environment a call)
+  auto want = [&](const char *key) { return tuned ? tune(key) : -1; };
   const double outputs = static_cast<double>(g.n) * g.to * g.ho * g.wo * g.c_out;
-  if (tune("wide") != 1 && 0.73 * item_cycles + 2383e-6 * outputs < 1.05 * L.cycles) return none;
+  const double item = 0.73 * item_cycles + 2383e-6 * outputs;
+  auto item_wins = [&](double wide) { return want("wide") != 1 && item < 1.05 * wide; };
+  // A small layer that the item kernel wins by the bound alone is spared the
+  // search: its call is bound by the host.  (0.999: the bound's rounding)
+  if (item_wins(0.999 * least_wide(g, wp))) return none;
+  WideLaunch L = best_wide(g, wp, std::min<uint64_t>(ws_cap, kScratchBytes), device_cus(),
+                           want("splits"), want("wide_fm"), want("wide_wm"));
+  if (L.fm == 0 || item_wins(L.cycles)) return none;
   const long bricks = static_cast<long>(g.n) * ((g.to + wp.bt - 1) / wp.bt) *
                       ((g.ho + wp.bh - 1) / wp.bh) * ((g.wo + wp.bw - 1) / wp.bw);
   const int c16_total = (g.c_in + 15) / 16, rows32 = (g.c_out + 31) / 32;
