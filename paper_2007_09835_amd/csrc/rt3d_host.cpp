@@ -1313,6 +1313,10 @@ struct WideLaunch {
 // reduction's start and a partial sum's byte, written and read back.
 constexpr double kWideStep[3] = {0, 223, 349}, kWideTile[3] = {0, 7645, 12850};
 constexpr double kWideLoad = 5.8, kWideLoadFree = 4817, kWideChunk = 670, kWideStart = 4450;
+// kWideSecondLaunch: what a split's second launch costs a layer that the item
+// kernel runs in one (small eager calls are bound by launches: 64->64 3x3x3 on
+// 4x14x14 took 10.5 us unsplit on the item kernel and 13.5 split on this one).
+constexpr double kWideSecondLaunch = 10000;
 constexpr double kWideReduceStart = 4700, kWidePartialBytes = 0.63;
 
 // The best launch shape of a wide plan, by a time model in cycles.  A
@@ -1323,7 +1327,7 @@ constexpr double kWideReduceStart = 4700, kWidePartialBytes = 0.63;
 // fitted to 110 layers of the C3D, R(2+1)D and S3D stacks at batch 1 to 32
 // (mean error 5.5%).
 WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cus, int want_splits,
-                     int want_fm, int want_wm) {
+                     int want_fm, int want_wm, double second_launch = 0) {
   WideLaunch best;
   best.wgs = cus;
   const long bricks = static_cast<long>(g.n) * ((g.to + wp.bt - 1) / wp.bt) *
@@ -1355,7 +1359,7 @@ WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cu
         if (n >= (1L << 24)) break;
         if (!want || s <= want) {
           double t = static_cast<double>((n + cus - 1) / cus) * (per * chunk + kWideTile[fm]) + kWideStart + load;
-          if (s > 1) t += kWideReduceStart + kWidePartialBytes / 1000 * 2.0 * static_cast<double>(s * per_split);
+          if (s > 1) t += second_launch + kWideReduceStart + kWidePartialBytes / 1000 * 2.0 * static_cast<double>(s * per_split);
           if (best_t < 0 || t < best_t || (want && s > best.splits)) {
             best_t = t;
             best.fm = fm;
@@ -1949,7 +1953,7 @@ WidePlan wide_plan_of(const rt3d_pack_info *info) {
 // one's (its own cycles x 0.73 plus 1.06 us per million outputs, 10% mean
 // error); the 5% margin keeps the item kernel where the two are close.
 WideLaunch plan_wide(const rt3d_conv3d_desc *d, const WidePlan &wp, uint64_t ws_cap,
-                     double item_cycles) {
+                     const Launch &item_launch) {
   WideLaunch none;
   if (wp.a_off == 0 || wp.rgb) return none;
   const int x_pitch = d->x_c_total != 0 ? d->x_c_total : d->c_in;
@@ -1959,13 +1963,14 @@ WideLaunch plan_wide(const rt3d_conv3d_desc *d, const WidePlan &wp, uint64_t ws_
   const bool tuned = std::getenv("RT3D_TUNE") != nullptr;   // (one look at the environment a call)
   auto want = [&](const char *key) { return tuned ? tune(key) : -1; };
   const double outputs = static_cast<double>(g.n) * g.to * g.ho * g.wo * g.c_out;
-  const double item = 0.73 * item_cycles + 2383e-6 * outputs;
+  const double item = 0.73 * item_launch.cycles + 2383e-6 * outputs;
   auto item_wins = [&](double wide) { return want("wide") != 1 && item < 1.05 * wide; };
   // A small layer that the item kernel wins by the bound alone is spared the
   // search: its call is bound by the host.  (0.999: the bound's rounding)
   if (item_wins(0.999 * least_wide(g, wp))) return none;
   WideLaunch L = best_wide(g, wp, std::min<uint64_t>(ws_cap, kScratchBytes), device_cus(),
-                           want("splits"), want("wide_fm"), want("wide_wm"));
+                           want("splits"), want("wide_fm"), want("wide_wm"),
+                           item_launch.splits > 1 ? 0 : kWideSecondLaunch);
   if (L.fm == 0 || item_wins(L.cycles)) return none;
   const long bricks = static_cast<long>(g.n) * ((g.to + wp.bt - 1) / wp.bt) *
                       ((g.ho + wp.bh - 1) / wp.bh) * ((g.wo + wp.bw - 1) / wp.bw);
@@ -2000,7 +2005,7 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   std::memcpy(&p, info->plan, sizeof(p));
   const Launch launch = plan_launch(d, p, info->variant, workspace ? ws_bytes : 0, info->packed_bytes - p.a_off);
   const WidePlan wp = wide_plan_of(info);
-  const WideLaunch wl = plan_wide(d, wp, workspace ? ws_bytes : 0, launch.cycles);
+  const WideLaunch wl = plan_wide(d, wp, workspace ? ws_bytes : 0, launch);
   const Geom g = geom_of(d);
   const Tiling &tl = p.tiling;
   const uint8_t *b = static_cast<const uint8_t *>(blob);
@@ -2344,7 +2349,7 @@ rt3d_status rt3d_conv3d_workspace_size(const rt3d_conv3d_desc *d, const rt3d_pac
   std::memcpy(&p, info->plan, sizeof(p));
   const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off);
   // enough for either kernel (the input's pitch may rule the wide one out)
-  *bytes = std::max(L.ws_bytes, plan_wide(d, wide_plan_of(info), UINT64_MAX, L.cycles).ws_bytes);
+  *bytes = std::max(L.ws_bytes, plan_wide(d, wide_plan_of(info), UINT64_MAX, L).ws_bytes);
   return ok();
 }
 
@@ -2369,7 +2374,7 @@ rt3d_status rt3d_kgs_conv3d_fwd_noalloc(const rt3d_conv3d_desc *d, const rt3d_pa
   // then the one rt3d_kgs_conv3d_fwd makes with that workspace.
   const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off);
   const uint64_t need =
-      std::max(L.ws_bytes, plan_wide(d, wide_plan_of(info), UINT64_MAX, L.cycles).ws_bytes);
+      std::max(L.ws_bytes, plan_wide(d, wide_plan_of(info), UINT64_MAX, L).ws_bytes);
   if (need > kScratchBytes)
     return fail(RT3D_ERR_UNSUPPORTED,
                 "this launch needs %llu bytes of split-K scratch; the no-allocation entry point "

@@ -117,3 +117,14 @@ def test_wide_layout_is_left_out(monkeypatch):
     assert a_off(3, "bf16", "small_mfw=1", thw=(4, 8, 44)) == 0
     for tune in ("wide=0", "slots=64", "dense_mfw=1", "cc=32"):
         assert a_off(32, "bf16", tune) == 0
+
+
+@pytest.mark.parametrize("c_in,c_out,thw,dtype", [(64, 64, (4, 14, 14), "bf16"), (64, 64, (4, 14, 14), "f16")])
+def test_small_layers_stay_in_one_launch(c_in, c_out, thw, dtype):
+    """A layer that one item-kernel launch serves is not split for a gain
+    smaller than a second launch: it asks for no workspace."""
+    d = rt3d.make_desc(1, c_in, c_out, thw, (3, 3, 3), (1, 1, 1), (1, 1, 1), (4, 4), dtype)
+    w = torch.zeros((c_out, c_in, 3, 3, 3), dtype={"bf16": torch.bfloat16, "f16": torch.float16}[dtype])
+    _, info = rt3d.rt3d_dense_pack(d, w)
+    assert _wide(info)[0] > 0                      # the layout is there
+    assert rt3d.rt3d_conv3d_workspace_size(d, info) == 0
