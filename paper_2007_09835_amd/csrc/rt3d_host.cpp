@@ -1509,13 +1509,18 @@ bool wide_wanted(const Geom &g, bool small, const Mask4 *m4) {
   return true;
 }
 
+// Bytes of the wide weights: 32-filter rows (an even count), steps, 1 KB each.
+uint64_t wide_weight_bytes(const Geom &g) {
+  return static_cast<uint64_t>(((g.c_out + 31) / 32 + 1) / 2 * 2) * g.ks * ((g.c_in + 15) / 16) * 1024;
+}
+
 // Steps in blob order (chunks, kernel positions, 16-channel slices).
 void build_wide_layout(const Geom &g, const WidePlan &wp, const uint8_t *w, const Mask4 *m4,
                        std::vector<uint8_t> &out) {
   const int c16_total = (g.c_in + 15) / 16;
-  const int frags = ((g.c_out + 31) / 32 + 1) / 2 * 2;
   const long stot = static_cast<long>(g.ks) * c16_total;
-  out.assign(static_cast<size_t>(frags) * stot * 1024, 0);
+  const size_t weights = wide_weight_bytes(g);
+  out.assign(weights, 0);
   std::vector<long> step_of(stot);   // [c16 slice][pos] -> step
   {
     long s = 0;
@@ -1546,6 +1551,7 @@ void build_wide_layout(const Geom &g, const WidePlan &wp, const uint8_t *w, cons
       out.insert(out.end(), reinterpret_cast<const uint8_t *>(&e), reinterpret_cast<const uint8_t *>(&e) + 4);
     }
   }
+  out.resize(std::max(out.size(), weights + kWideTail), 0);
 }
 
 // Assemble header + canonical + layout sections.  With out == nullptr only
@@ -1948,17 +1954,19 @@ WidePlan wide_plan_of(const rt3d_pack_info *info) {
 // The wide kernel's launch for this call, fm = 0 when the call runs on the
 // item kernel: no wide layout in the blob, an input pitch or offset that is
 // not a multiple of 8 channels (the staging loads whole 16-byte pieces), a
-// batch item of 4 GiB or more (32-bit halo offsets), or an item-kernel launch
+// blob that ends less than kWideTail bytes behind the weights, a batch item of 4 GiB or more (32-bit halo offsets), or an item-kernel launch
 // that is modelled faster.  The item kernel's model was fitted like the wide
 // one's (its own cycles x 0.73 plus 1.06 us per million outputs, 10% mean
 // error); the 5% margin keeps the item kernel where the two are close.
-WideLaunch plan_wide(const rt3d_conv3d_desc *d, const WidePlan &wp, uint64_t ws_cap,
+WideLaunch plan_wide(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, uint64_t ws_cap,
                      const Launch &item_launch) {
+  const WidePlan wp = wide_plan_of(info);
   WideLaunch none;
   if (wp.a_off == 0 || wp.rgb) return none;
   const int x_pitch = d->x_c_total != 0 ? d->x_c_total : d->c_in;
   if (x_pitch % 8 != 0 || d->x_c_off % 8 != 0) return none;
   const Geom g = geom_of(d);
+  if (info->packed_bytes < wp.a_off + wide_weight_bytes(g) + kWideTail) return none;
   if (static_cast<double>(g.t) * g.h * g.w * x_pitch * 2 >= 4.29e9) return none;
   const bool tuned = std::getenv("RT3D_TUNE") != nullptr;   // (one look at the environment a call)
   auto want = [&](const char *key) { return tuned ? tune(key) : -1; };
@@ -2005,7 +2013,7 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   std::memcpy(&p, info->plan, sizeof(p));
   const Launch launch = plan_launch(d, p, info->variant, workspace ? ws_bytes : 0, info->packed_bytes - p.a_off);
   const WidePlan wp = wide_plan_of(info);
-  const WideLaunch wl = plan_wide(d, wp, workspace ? ws_bytes : 0, launch);
+  const WideLaunch wl = plan_wide(d, info, workspace ? ws_bytes : 0, launch);
   const Geom g = geom_of(d);
   const Tiling &tl = p.tiling;
   const uint8_t *b = static_cast<const uint8_t *>(blob);
@@ -2094,9 +2102,8 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
     WideArgs wa{};
     static_cast<ConvArgs &>(wa) = a;
     wa.a = b + wp.a_off;
-    wa.stage_tab = reinterpret_cast<const uint32_t *>(
-        b + wp.a_off + static_cast<uint64_t>(((g.c_out + 31) / 32 + 1) / 2 * 2) * g.ks * ((g.c_in + 15) / 16) * 1024);
-    wa.a_bytes = ((g.c_out + 31) / 32 + 1) / 2 * 2 * g.ks * ((g.c_in + 15) / 16) * 1024;
+    wa.stage_tab = reinterpret_cast<const uint32_t *>(b + wp.a_off + wide_weight_bytes(g));
+    wa.a_bytes = static_cast<int32_t>(wide_weight_bytes(g));
     wa.bt = wp.bt; wa.bh = wp.bh; wa.bw = wp.bw;
     wa.nbt = (g.to + wp.bt - 1) / wp.bt;
     wa.nbh = (g.ho + wp.bh - 1) / wp.bh;
@@ -2349,7 +2356,7 @@ rt3d_status rt3d_conv3d_workspace_size(const rt3d_conv3d_desc *d, const rt3d_pac
   std::memcpy(&p, info->plan, sizeof(p));
   const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off);
   // enough for either kernel (the input's pitch may rule the wide one out)
-  *bytes = std::max(L.ws_bytes, plan_wide(d, wide_plan_of(info), UINT64_MAX, L).ws_bytes);
+  *bytes = std::max(L.ws_bytes, plan_wide(d, info, UINT64_MAX, L).ws_bytes);
   return ok();
 }
 
@@ -2374,7 +2381,7 @@ rt3d_status rt3d_kgs_conv3d_fwd_noalloc(const rt3d_conv3d_desc *d, const rt3d_pa
   // then the one rt3d_kgs_conv3d_fwd makes with that workspace.
   const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off);
   const uint64_t need =
-      std::max(L.ws_bytes, plan_wide(d, wide_plan_of(info), UINT64_MAX, L).ws_bytes);
+      std::max(L.ws_bytes, plan_wide(d, info, UINT64_MAX, L).ws_bytes);
   if (need > kScratchBytes)
     return fail(RT3D_ERR_UNSUPPORTED,
                 "this launch needs %llu bytes of split-K scratch; the no-allocation entry point "

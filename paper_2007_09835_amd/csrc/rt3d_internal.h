@@ -108,7 +108,8 @@ struct ConvArgs {
 // channel chunks of 16 * c16 channels, then kernel positions, then the
 // chunk's 16-channel slices.
 // After the weights: the stage table, u32 per 16-byte slot of a halo buffer,
-// t | h << 9 | w << 18 | piece << 27 in the halo, all ones for padding.
+// t | h << 9 | w << 18 | piece << 27 in the halo, all ones for padding.  The
+// section ends kWideTail bytes behind the weights at the earliest.
 struct WidePlan {
   uint64_t a_off;
   uint8_t bt, bh, bw;      // output brick
@@ -134,6 +135,36 @@ struct WideArgs : ConvArgs {
 };
 
 constexpr int kWideSteps = 128;   // most K-steps of one part and chunk
+constexpr int kWideRing = 6;      // weight fragments in flight per row (steps); even
+constexpr int kWideTail = (kWideRing - 1) * 7 * 1024;  // bytes a wave may read past the weights
+
+// A wave's walk through the wide weights: the byte offset of the next 1 KB
+// fragment of each of its FM 32-filter rows.  The wave multiplies steps kpart,
+// kpart + WK, ... of every channel chunk, and fetches kWideRing - 1 steps ahead
+// of the multiplication: past its last step the fetched values are unused, but
+// the load is made.  (The offset is a scalar one, which a buffer load's range
+// check need not cover; a min per step to hold it back cost 0.5-1% of the
+// kernel's time.)  So a blob holds at least kWideTail bytes behind the weights:
+// a fetch advances by at most 2 * WK - 1 steps.
+template <int FM, int WK>
+struct WideWalk {
+  uint32_t off[FM];
+  uint32_t jump;           // added at a chunk's end: WK need not divide its steps
+  int full, left;          // steps of this part in a whole chunk, and to the next one
+
+  // row: first 32-filter row; sc_full: steps of a whole chunk; n_full: this part's share of them.
+  constexpr void start(int row, int stot, int ch0, int sc_full, int n_full, int kpart) {
+    jump = static_cast<uint32_t>(sc_full - n_full * WK) * 1024u;
+    full = left = n_full;
+    for (int i = 0; i < FM; ++i)
+      off[i] = (static_cast<uint32_t>(row + i) * stot + ch0 * sc_full + kpart) * 1024u;
+  }
+  constexpr void next() {
+    const uint32_t adv = WK * 1024u + (left == 1 ? jump : 0u);
+    left = left == 1 ? full : left - 1;
+    for (int i = 0; i < FM; ++i) off[i] += adv;
+  }
+};
 // LDS of the wide kernel: two halo buffers, the epilogue tile of four waves
 // (rows of 32 fp32 filters and 16 bytes), and two sets of epilogue tables
 // (output and first slot of 128 slots, bias of up to 256 filters).

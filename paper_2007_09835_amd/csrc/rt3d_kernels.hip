@@ -1081,7 +1081,7 @@ __global__ __launch_bounds__(512, 2) void wide_kernel(WideArgs a) {
   using V8 = std::conditional_t<std::is_same_v<T, __bf16>, bf16x8, f16x8>;
   constexpr int SLOTS = 32 * FN;
   constexpr int WM = 4 / WK;
-  constexpr int DA = 6;                       // weight ring (steps); even
+  constexpr int DA = kWideRing;
   constexpr int TROW = kWideTileRow;          // epilogue tile: bytes per slot (32 filters)
   constexpr int MWG = 32 * FM * WM;           // filters per workgroup
   extern __shared__ __align__(16) uint8_t lds[];
@@ -1251,26 +1251,14 @@ __global__ __launch_bounds__(512, 2) void wide_kernel(WideArgs a) {
   const int sc_full = a.ks * a.c16;
   const int sc_last = a.ks * (a.c16_total - (a.nchunks - 1) * a.c16);
   const int n_full = (sc_full - kpart + WK - 1) / WK, n_last = (sc_last - kpart + WK - 1) / WK;
-  // Weight stream: steps kpart, kpart + WK, ... of each chunk, read at a
-  // scalar offset from the section's start.  a_left counts the steps to the
-  // next chunk, where the offset advances by a_jump more (WK need not divide
-  // a chunk's steps).  Past the section's end the loads return zeros, which
-  // are never used.
+  // Weight stream, read at a scalar offset from the section's start.
   const __amdgpu_buffer_rsrc_t ares =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.a), 0, a.a_bytes, 0x00020000);
   const uint32_t lane16 = static_cast<uint32_t>(lane) * 16u;
-  const uint32_t a_jump = static_cast<uint32_t>(sc_full - n_full * WK) * 1024u;
-  uint32_t a_off[FM];
-  int a_left = n_full;
+  WideWalk<FM, WK> walk;
   V8 ra[DA][FM], rb[2][FN];
   auto fetch_a = [&](int slot, int i) {
-    ra[slot][i] = __builtin_bit_cast(V8, __builtin_amdgcn_raw_buffer_load_b128(ares, lane16, a_off[i], 0));
-  };
-  auto next_a = [&]() {
-    const uint32_t adv = WK * 1024u + (a_left == 1 ? a_jump : 0u);
-    a_left = a_left == 1 ? n_full : a_left - 1;
-#pragma unroll
-    for (int i = 0; i < FM; ++i) a_off[i] += adv;
+    ra[slot][i] = __builtin_bit_cast(V8, __builtin_amdgcn_raw_buffer_load_b128(ares, lane16, walk.off[i], 0));
   };
   int ch0, ch1;
   bool active;
@@ -1280,15 +1268,12 @@ __global__ __launch_bounds__(512, 2) void wide_kernel(WideArgs a) {
     const int wt = wg.tg * WM + wm;
     active = wt < a.wave_tiles;
     split_range(a, wg.split, ch0, ch1);
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-      a_off[i] = (static_cast<uint32_t>((active ? wt : 0) * FM + i) * a.stot + ch0 * sc_full + kpart) * 1024u;
-    a_left = n_full;
+    walk.start((active ? wt : 0) * FM, a.stot, ch0, sc_full, n_full, kpart);
 #pragma unroll
     for (int d = 0; d < DA - 1; ++d) {
 #pragma unroll
       for (int i = 0; i < FM; ++i) fetch_a(d, i);
-      next_a();
+      walk.next();
     }
   };
   int id = static_cast<int>(blockIdx.x), parity = 0;
@@ -1382,7 +1367,7 @@ __global__ __launch_bounds__(512, 2) void wide_kernel(WideArgs a) {
       }
       if constexpr (J == FN / 2) off_next = step_off(li + 2);
       if constexpr (J == FN - 1) {
-        if (refill) next_a();
+        if (refill) walk.next();
       }
       __builtin_amdgcn_sched_barrier(0);
     });
