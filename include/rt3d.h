@@ -196,6 +196,29 @@ rt3d_status rt3d_kgs_unpack(const rt3d_conv3d_desc *desc, const rt3d_pack_info *
 rt3d_status rt3d_conv3d_workspace_size(const rt3d_conv3d_desc *desc,
                                        const rt3d_pack_info *info, uint64_t *bytes);
 
+/* The launch that a forward call of this layer makes at desc->n with this
+ * much workspace (for profiles and tests).  Host only. */
+typedef enum {
+    RT3D_KERNEL_ITEM = 0,  /* item kernels (every dtype) */
+    RT3D_KERNEL_SMALL = 1, /* small-input-channel kernel (16-bit, c_in <= 4) */
+    RT3D_KERNEL_WIDE = 2,  /* wide kernel (16-bit) */
+    RT3D_KERNEL_RGB = 3    /* RGB kernel (16-bit, c_in <= 4) */
+} rt3d_kernel;
+
+typedef struct {
+    int32_t kernel;           /* rt3d_kernel */
+    int32_t bt, bh, bw;       /* output brick of a workgroup */
+    int32_t chunk;            /* input channels per staged chunk */
+    int32_t rows;             /* filters of a wave tile */
+    int32_t wm, wk;           /* waves along the filters, parts of the reduction in a workgroup */
+    int32_t splits;           /* channel splits across workgroups */
+    int32_t order;            /* logical workgroup order: 0 bricks fastest, 1 filters fastest */
+    uint64_t workspace_bytes; /* workspace it uses */
+} rt3d_launch_info;
+
+rt3d_status rt3d_conv3d_launch_info(const rt3d_conv3d_desc *desc, const rt3d_pack_info *info,
+                                    uint64_t workspace_bytes, rt3d_launch_info *out);
+
 /* KGS (and vanilla) sparse forward.  blob_dev: device copy of the blob that
  * rt3d_kgs_pack wrote with this desc (info from that call).  With n == 0
  * nothing is read or written and the device pointers may be NULL.  x, y, residual

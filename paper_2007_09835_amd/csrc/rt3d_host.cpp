@@ -1994,6 +1994,22 @@ WideLaunch plan_wide(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, uint
   return L;
 }
 
+// Bytes of the item kernel's weight section (the wide section, when there is
+// one, comes right behind it).
+uint64_t item_bytes(const rt3d_pack_info *info, const Plan &p) {
+  const WidePlan wp = wide_plan_of(info);
+  return (wp.a_off != 0 ? wp.a_off : info->packed_bytes) - p.a_off;
+}
+
+// Layers with up to 4 input channels: the RGB kernel, except where a residual
+// is added or an output voxel's filters are not whole 16-byte words (the
+// small-channel kernel).
+bool takes_rgb(const rt3d_conv3d_desc *d, const WidePlan &wp) {
+  const int y_pitch = d->y_c_total != 0 ? d->y_c_total : d->c_out;
+  return wp.a_off != 0 && wp.rgb && !(d->flags & RT3D_RESIDUAL) && tune("wide") != 0 &&
+         (d->c_out | y_pitch | d->y_c_off) % 8 == 0;
+}
+
 rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, const void *blob,
                      const void *x, const float *bias, const void *residual, void *y,
                      void *workspace, uint64_t ws_bytes, void *stream, bool sparse) {
@@ -2011,7 +2027,7 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
     return fail(RT3D_ERR_INVALID_ARG, "device pointers must be 16-byte aligned");
   Plan p;
   std::memcpy(&p, info->plan, sizeof(p));
-  const Launch launch = plan_launch(d, p, info->variant, workspace ? ws_bytes : 0, info->packed_bytes - p.a_off);
+  const Launch launch = plan_launch(d, p, info->variant, workspace ? ws_bytes : 0, item_bytes(info, p));
   const WidePlan wp = wide_plan_of(info);
   const WideLaunch wl = plan_wide(d, info, workspace ? ws_bytes : 0, launch);
   const Geom g = geom_of(d);
@@ -2035,7 +2051,7 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   a.gmap = info->variant == kVarKgsUnion16 && p.gmap ? a.keep : nullptr;
   a.gmap_slots = a.gmap ? p.wave_tiles * 4 * p.mfw : 0;
   a.a = b + p.a_off;
-  a.a_bytes = static_cast<int32_t>(std::min<uint64_t>(info->packed_bytes - p.a_off, 0x7fffffffu));
+  a.a_bytes = static_cast<int32_t>(std::min<uint64_t>(item_bytes(info, p), 0x7fffffffu));
   a.n = g.n; a.c_in = g.c_in; a.c_out = g.c_out; a.t = g.t; a.h = g.h; a.w = g.w;
   a.to = g.to; a.ho = g.ho; a.wo = g.wo;
   a.st = g.st; a.sh = g.sh; a.sw = g.sw; a.pt = g.pt; a.ph = g.ph; a.pw = g.pw;
@@ -2071,10 +2087,7 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   if (static_cast<long>(a.n) * a.nbt * a.nbh * a.nbw * a.ntg * a.splits >= (1L << 24))
     return fail(RT3D_ERR_UNSUPPORTED, "layer needs 2^24 or more workgroups");
   int e;
-  // Layers with up to 4 input channels: the RGB kernel, except where a
-  // residual is added or an output voxel's filters are not whole 16-byte
-  // words (the small-channel kernel).
-  if (wp.a_off != 0 && wp.rgb && !residual && tune("wide") != 0 && (g.c_out | a.y_pitch | a.y_off) % 8 == 0) {
+  if (takes_rgb(d, wp)) {
     const RgbShape r = rgb_shape(g);
     WideArgs ra{};
     static_cast<ConvArgs &>(ra) = a;
@@ -2354,9 +2367,32 @@ rt3d_status rt3d_conv3d_workspace_size(const rt3d_conv3d_desc *d, const rt3d_pac
     return fail(RT3D_ERR_BLOB_MISMATCH, "info does not belong to this layer description");
   Plan p;
   std::memcpy(&p, info->plan, sizeof(p));
-  const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off);
+  const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, item_bytes(info, p));
   // enough for either kernel (the input's pitch may rule the wide one out)
   *bytes = std::max(L.ws_bytes, plan_wide(d, info, UINT64_MAX, L).ws_bytes);
+  return ok();
+}
+
+rt3d_status rt3d_conv3d_launch_info(const rt3d_conv3d_desc *d, const rt3d_pack_info *info,
+                                    uint64_t workspace_bytes, rt3d_launch_info *out) {
+  rt3d_status st = check_desc(d, false);
+  if (st != RT3D_OK) return st;
+  if (!info || !out) return fail(RT3D_ERR_INVALID_ARG, "info and out must be non-NULL");
+  if (info->magic != kMagic || info->version != kVersion || info->desc_hash != desc_hash(d))
+    return fail(RT3D_ERR_BLOB_MISMATCH, "info does not belong to this layer description");
+  Plan p;
+  std::memcpy(&p, info->plan, sizeof(p));
+  const WidePlan wp = wide_plan_of(info);
+  const Launch L = plan_launch(d, p, info->variant, workspace_bytes, item_bytes(info, p));
+  const WideLaunch W = plan_wide(d, info, workspace_bytes, L);
+  if (takes_rgb(d, wp))
+    *out = {RT3D_KERNEL_RGB, 4, 4, 32, d->c_in, 64, 1, 1, 1, 0, 0};
+  else if (W.fm > 0)
+    *out = {RT3D_KERNEL_WIDE, wp.bt, wp.bh, wp.bw, wp.c16 * 16, 32 * W.fm, W.wm, W.wk, W.splits, W.order, W.ws_bytes};
+  else
+    *out = {info->variant == kVarSmallDense16 || info->variant == kVarSmallKgs16 ? RT3D_KERNEL_SMALL
+                                                                                 : RT3D_KERNEL_ITEM,
+            p.tiling.bt, p.tiling.bh, p.tiling.bw, p.tiling.cc, 16 * p.mfw, L.wpw, 1, L.splits, L.order, L.ws_bytes};
   return ok();
 }
 
@@ -2379,7 +2415,7 @@ rt3d_status rt3d_kgs_conv3d_fwd_noalloc(const rt3d_conv3d_desc *d, const rt3d_pa
   std::memcpy(&p, info->plan, sizeof(p));
   // The split count a caller workspace of any size would get: the launch is
   // then the one rt3d_kgs_conv3d_fwd makes with that workspace.
-  const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, info->packed_bytes - p.a_off);
+  const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, item_bytes(info, p));
   const uint64_t need =
       std::max(L.ws_bytes, plan_wide(d, info, UINT64_MAX, L).ws_bytes);
   if (need > kScratchBytes)

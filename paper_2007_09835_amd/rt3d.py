@@ -37,7 +37,7 @@ DTYPE_CODES = {"f32": RT3D_F32, "bf16": RT3D_BF16, "f16": RT3D_F16}
 EXPORTED = (
     "rt3d_status_string", "rt3d_last_error_detail", "rt3d_conv3d_out_shape",
     "rt3d_kgs_pack_size", "rt3d_kgs_pack", "rt3d_kgs_unpack", "rt3d_conv3d_workspace_size",
-    "rt3d_kgs_conv3d_fwd", "rt3d_kgs_conv3d_fwd_noalloc", "rt3d_dense_pack_size", "rt3d_dense_pack", "rt3d_conv3d_dense_fwd",
+    "rt3d_conv3d_launch_info", "rt3d_kgs_conv3d_fwd", "rt3d_kgs_conv3d_fwd_noalloc", "rt3d_dense_pack_size", "rt3d_dense_pack", "rt3d_conv3d_dense_fwd",
     "rt3d_maxpool3d_fwd", "rt3d_group_units", "rt3d_group_workspace_size", "rt3d_group_reweight",
 )
 
@@ -73,6 +73,15 @@ class PackInfo(ctypes.Structure):
     ]
 
 
+KERNELS = ("item", "small", "wide", "rgb")
+
+
+class LaunchInfo(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_int32) for name in (
+        "kernel", "bt", "bh", "bw", "chunk", "rows", "wm", "wk", "splits", "order")] + [
+        ("workspace_bytes", ctypes.c_uint64)]
+
+
 class GroupDesc(ctypes.Structure):
     _fields_ = [(name, ctypes.c_int32) for name in (
         "c_out", "c_in", "kt", "kh", "kw", "g_m", "g_n", "dtype", "norm", "scope")]
@@ -103,6 +112,7 @@ def load():
         "rt3d_kgs_pack": ([D, vp, vp, vp, u64, I], ctypes.c_int),
         "rt3d_kgs_unpack": ([D, I, vp, vp], ctypes.c_int),
         "rt3d_conv3d_workspace_size": ([D, I, P(u64)], ctypes.c_int),
+        "rt3d_conv3d_launch_info": ([D, I, u64, P(LaunchInfo)], ctypes.c_int),
         "rt3d_kgs_conv3d_fwd": ([D, I, vp, vp, vp, vp, vp, vp, u64, vp], ctypes.c_int),
         "rt3d_kgs_conv3d_fwd_noalloc": ([D, I, vp, vp, vp, vp, vp, vp], ctypes.c_int),
         "rt3d_dense_pack_size": ([D, P(u64)], ctypes.c_int),
@@ -224,6 +234,14 @@ def rt3d_conv3d_workspace_size(desc: Conv3dDesc, info: PackInfo) -> int:
     _check(load().rt3d_conv3d_workspace_size(ctypes.byref(desc), ctypes.byref(info),
                                              ctypes.byref(out)))
     return out.value
+
+
+def rt3d_conv3d_launch_info(desc: Conv3dDesc, info: PackInfo, workspace_bytes: int = 2 ** 64 - 1) -> LaunchInfo:
+    """The launch a forward call makes with this much workspace (default: any)."""
+    out = LaunchInfo()
+    _check(load().rt3d_conv3d_launch_info(ctypes.byref(desc), ctypes.byref(info), workspace_bytes,
+                                          ctypes.byref(out)))
+    return out
 
 
 def rt3d_kgs_conv3d_fwd(desc: Conv3dDesc, info: PackInfo, blob_dev, x, bias, residual, y,

@@ -1,0 +1,51 @@
+"""The launch a forward call makes, as rt3d_conv3d_launch_info reports it: what
+a blob holds for the wide kernel changes nothing for the calls that stay on
+the item kernel.  Host only (the planner's figures for 256 compute units)."""
+import random
+
+import pytest
+import torch
+
+from paper_2007_09835_amd import build, rt3d
+
+
+@pytest.fixture(scope="module", autouse=True)
+def built():
+    build.build(force=False)
+
+
+@pytest.fixture(autouse=True)
+def no_tune(monkeypatch):
+    monkeypatch.delenv("RT3D_TUNE", raising=False)
+
+
+def pack(c_in, c_out, thw, k, n=1, dtype="bf16", **kw):
+    d = rt3d.make_desc(n, c_in, c_out, thw, k, pad=tuple(v // 2 for v in k), dtype=dtype, **kw)
+    w = torch.zeros((c_out, c_in, *k), dtype=torch.bfloat16 if dtype == "bf16" else torch.float16)
+    return d, rt3d.rt3d_dense_pack(d, w)[1]
+
+
+def shapes(count, seed):
+    rng = random.Random(seed)
+    fixed = [(576, 256, (4, 14, 14), (3, 1, 1), 1), (128, 288, (8, 28, 28), (1, 3, 3), 1)]
+    for _ in range(count):
+        k = rng.choice([(3, 3, 3), (1, 3, 3), (3, 1, 1), (1, 1, 1)])
+        s = rng.choice([7, 14, 28])
+        fixed.append((rng.randint(2, 40) * 8, rng.randint(2, 40) * 8, (rng.randint(2, 8), s, s), k,
+                      rng.choice([1, 1, 2, 4, 8])))
+    return fixed
+
+
+def test_item_launch_does_not_depend_on_the_wide_section(monkeypatch):
+    """With a pitch that the wide kernel cannot read, the launch is the one of
+    a blob without the wide section, its workgroup order included."""
+    for c_in, c_out, thw, k, n in shapes(40, 1):
+        d, both = pack(c_in, c_out, thw, k, n)
+        monkeypatch.setenv("RT3D_TUNE", "wide=0")
+        _, alone = pack(c_in, c_out, thw, k, n)
+        monkeypatch.delenv("RT3D_TUNE")
+        d.x_c_total = c_in + 4
+        assert both.packed_bytes > alone.packed_bytes
+        a, b = (bytes(rt3d.rt3d_conv3d_launch_info(d, i)) for i in (both, alone))
+        assert a == b, (c_in, c_out, thw, k, n)
+        assert rt3d.rt3d_conv3d_launch_info(d, both).kernel == rt3d.KERNELS.index("item")
