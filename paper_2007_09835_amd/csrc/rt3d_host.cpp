@@ -585,38 +585,50 @@ int kgs_tile_width(const Geom &g, const Tiling &tl, const Mask4 *m4) {
 // C3D and R(2+1)D layers on MI355X.  wgs: workgroups of one split;
 // per_cu_split / per_cu_whole: resident workgroups per CU of split and
 // unsplit launches; cus: compute units.
-int model_splits(const Geom &g, const Tiling &tl, int mfw, double chunk_steps, uint32_t variant,
-                 long wgs, int per_cu_split, int per_cu_whole, long cus, double *cycles = nullptr) {
-  const long total_vox = static_cast<long>(g.n) * g.to * g.ho * g.wo;
-  const double partial_bytes = 2.0 * static_cast<double>(total_vox) * ((g.c_out + 3) / 4 * 4) * 4;
-  constexpr double kFixed = 12000, kReduce = 9600, kShare = 0.2, kPartialBytesPerCycle = 4200;
-  // Pair steps read twice the items of a union step (an estimate until
-  // measured per layer).
-  const double step_cycles = variant == kVarKgsPair16 ? 600.0
-                             : (mfw == 1 ? 380.0 : (mfw == 2 ? 555.0 : 815.0));
-  // A chunk costs its K-steps, but no less than the exposed latency of its
-  // halo load, plus the barriers and LDS commit around it.
-  constexpr double kChunkLatency = 5000, kChunkFixed = 2000;
-  const double chunk_cycles = std::max(chunk_steps * step_cycles, kChunkLatency) + kChunkFixed;
-  int splits = 1;
-  double best = -1;
-  for (int s = 1; s <= tl.nchunks; ++s) {
-    if (s > 1 && (tl.nchunks + s - 1) / s == (tl.nchunks + s - 2) / (s - 1)) continue;  // same chunks per WG
+struct SplitModel {
+  int nchunks;
+  long wgs, per_cu_split, per_cu_whole, cus;
+  double partial_bytes, chunk_cycles;
+
+  SplitModel(const Geom &g, const Tiling &tl, int mfw, double chunk_steps, uint32_t variant, long wgs_,
+             int per_cu_split_, int per_cu_whole_, long cus_)
+      : nchunks(tl.nchunks), wgs(wgs_), per_cu_split(per_cu_split_), per_cu_whole(per_cu_whole_), cus(cus_) {
+    partial_bytes = 2.0 * static_cast<double>(static_cast<long>(g.n) * g.to * g.ho * g.wo) * ((g.c_out + 3) / 4 * 4) * 4;
+    // Pair steps read twice the items of a union step (an estimate until
+    // measured per layer).
+    const double step_cycles = variant == kVarKgsPair16 ? 600.0
+                               : (mfw == 1 ? 380.0 : (mfw == 2 ? 555.0 : 815.0));
+    // A chunk costs its K-steps, but no less than the exposed latency of its
+    // halo load, plus the barriers and LDS commit around it.
+    constexpr double kChunkLatency = 5000, kChunkFixed = 2000;
+    chunk_cycles = std::max(chunk_steps * step_cycles, kChunkLatency) + kChunkFixed;
+  }
+
+  double cycles(int s) const {
+    constexpr double kFixed = 12000, kReduce = 9600, kShare = 0.2, kPartialBytesPerCycle = 4200;
     const long n = wgs * s;
     const long per_cu = s > 1 ? per_cu_split : per_cu_whole;
     const long per = std::min<long>((n + cus - 1) / cus, per_cu);          // workgroups per CU at once
     const long rounds = (n + cus * per - 1) / (cus * per);
-    const double t = rounds * (kFixed + ((tl.nchunks + s - 1) / s) * chunk_cycles *
-                                            (1.0 + kShare * static_cast<double>(per - 1))) +
-                     (s > 1 ? kReduce + s * partial_bytes / kPartialBytesPerCycle : 0.0);
-    if (best < 0 || t < best) {
-      best = t;
-      splits = s;
-    }
+    return rounds * (kFixed + ((nchunks + s - 1) / s) * chunk_cycles *
+                                  (1.0 + kShare * static_cast<double>(per - 1))) +
+           (s > 1 ? kReduce + s * partial_bytes / kPartialBytesPerCycle : 0.0);
   }
-  if (cycles) *cycles = best;
-  return splits;
-}
+
+  int best() const {
+    int splits = 1;
+    double least = -1;
+    for (int s = 1; s <= nchunks; ++s) {
+      if (s > 1 && (nchunks + s - 1) / s == (nchunks + s - 2) / (s - 1)) continue;  // same chunks per WG
+      const double t = cycles(s);
+      if (least < 0 || t < least) {
+        least = t;
+        splits = s;
+      }
+    }
+    return splits;
+  }
+};
 
 // Filter rows (of 16) per wave tile of the item kernels, then the brick.
 //
@@ -677,8 +689,8 @@ ItemPlan item_plan(const Geom &g, const Mask4 *m4, bool small) {
         long steps = 0;
         for (int ch = 0; ch < t.nchunks; ++ch)
           steps += ((std::min(t.cc, g.c_in - ch * t.cc) + 3) / 4 * g.ks + 7) / 8;
-        return model_splits(g, t, mfw, static_cast<double>(steps) / t.nchunks, kVarDenseItems16,
-                            bricks * ntg, 2, 2, 256);
+        return SplitModel(g, t, mfw, static_cast<double>(steps) / t.nchunks, kVarDenseItems16,
+                          bricks * ntg, 2, 2, 256).best();
       };
       if (splits_at(ip.mfw) > 1 && splits_at(1) == 1) ip.mfw = 1;
     }
@@ -1927,13 +1939,14 @@ Launch plan_launch(const rt3d_conv3d_desc *d, const Plan &p, uint32_t variant, u
   if (per_cu_split <= 0) per_cu_split = 2;
   if (per_cu_whole <= 0) per_cu_whole = per_cu_split;
   const double chunk_steps = p.tile_steps > 0 ? static_cast<double>(p.tile_steps) / tl.nchunks : 24.0;
-  int splits = model_splits(g, tl, p.mfw, chunk_steps, variant, wgs, per_cu_split, per_cu_whole,
-                            device_cus(), &L.cycles);
+  const SplitModel model(g, tl, p.mfw, chunk_steps, variant, wgs, per_cu_split, per_cu_whole, device_cus());
+  int splits = model.best();
   if (tune("splits") > 0) splits = std::max(1, std::min(tl.nchunks, tune("splits")));
   const long total_vox = static_cast<long>(g.n) * g.to * g.ho * g.wo;
   const uint64_t per_split = static_cast<uint64_t>(total_vox) * ((g.c_out + 3) / 4 * 4) * 4;
   while (splits > 1 && per_split * splits > ws_cap) --splits;
   L.splits = splits;
+  L.cycles = model.cycles(splits);   // of the launch that is made: the workspace may have cut the splits
   L.ws_bytes = splits > 1 ? per_split * splits : 0;
   const double a_unit = static_cast<double>(a_bytes) / (static_cast<double>(ntg) * splits);
   const double x_unit = static_cast<double>(tl.ht) * tl.hh * tl.hw * tl.cc * g.es * tl.nchunks / splits;

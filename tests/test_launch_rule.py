@@ -49,3 +49,16 @@ def test_item_launch_does_not_depend_on_the_wide_section(monkeypatch):
         a, b = (bytes(rt3d.rt3d_conv3d_launch_info(d, i)) for i in (both, alone))
         assert a == b, (c_in, c_out, thw, k, n)
         assert rt3d.rt3d_conv3d_launch_info(d, both).kernel == rt3d.KERNELS.index("item")
+
+
+@pytest.mark.parametrize("c_in,c_out,thw,k", [(576, 256, (4, 14, 14), (3, 1, 1)), (216, 248, (5, 7, 7), (3, 1, 1)),
+                                              (296, 80, (2, 28, 28), (1, 3, 3))])
+def test_without_workspace_the_kernels_are_compared_as_they_run(c_in, c_out, thw, k):
+    """A split item launch is no rival where there is no workspace for it: the
+    item kernel would walk every channel chunk in one workgroup, which the wide
+    kernel's four parts of the reduction beat."""
+    d, info = pack(c_in, c_out, thw, k)
+    split, whole = rt3d.rt3d_conv3d_launch_info(d, info), rt3d.rt3d_conv3d_launch_info(d, info, 0)
+    assert split.kernel == rt3d.KERNELS.index("item") and split.splits > 1
+    assert whole.kernel == rt3d.KERNELS.index("wide")
+    assert whole.splits == 1 and whole.workspace_bytes == 0
