@@ -192,7 +192,8 @@ rt3d_status rt3d_kgs_unpack(const rt3d_conv3d_desc *desc, const rt3d_pack_info *
  * partial sums go to this caller-owned device buffer (16-byte aligned) and a
  * second kernel adds them in a fixed order, so results stay bit-reproducible.
  * A forward call given less workspace (or none) uses fewer splits; it never
- * fails for lack of workspace. */
+ * fails for lack of workspace.  A desc with x_c_total = 0 is sized for every
+ * input pitch that a call may have. */
 rt3d_status rt3d_conv3d_workspace_size(const rt3d_conv3d_desc *desc,
                                        const rt3d_pack_info *info, uint64_t *bytes);
 

@@ -2381,8 +2381,15 @@ rt3d_status rt3d_conv3d_workspace_size(const rt3d_conv3d_desc *d, const rt3d_pac
   Plan p;
   std::memcpy(&p, info->plan, sizeof(p));
   const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, item_bytes(info, p));
-  // enough for either kernel (the input's pitch may rule the wide one out)
+  // Enough for either kernel.  A desc that names no input pitch stands for
+  // every pitch: a ragged channel count is counted on a pitch of whole 16-byte
+  // pieces too, on which the wide kernel can run.
   *bytes = std::max(L.ws_bytes, plan_wide(d, info, UINT64_MAX, L).ws_bytes);
+  if (d->x_c_total == 0 && d->c_in % 8 != 0) {
+    rt3d_conv3d_desc padded = *d;
+    padded.x_c_total = (d->c_in + 7) / 8 * 8;
+    *bytes = std::max(*bytes, plan_wide(&padded, info, UINT64_MAX, L).ws_bytes);
+  }
   return ok();
 }
 

@@ -62,3 +62,25 @@ def test_without_workspace_the_kernels_are_compared_as_they_run(c_in, c_out, thw
     assert split.kernel == rt3d.KERNELS.index("item") and split.splits > 1
     assert whole.kernel == rt3d.KERNELS.index("wide")
     assert whole.splits == 1 and whole.workspace_bytes == 0
+
+
+def test_workspace_covers_every_input_pitch():
+    """A layer's workspace is asked for before its input's pitch is known.
+    Ragged channel counts run on the wide kernel only where the pitch is padded
+    to 8 channels: the size without a pitch covers that launch too."""
+    rng = random.Random(3)
+    cases = [(500, 64, (2, 14, 14), (1, 3, 3), 4, 1)]
+    for c_in, c_out, thw, k, n in shapes(60, 4):
+        cases.append((c_in - rng.randint(1, 7) if c_in > 24 else 21, c_out, thw, k, n, rng.choice([1, n])))
+    grew = 0
+    for c_in, c_out, thw, k, n, run_n in cases:
+        d, info = pack(c_in, c_out, thw, k, n)
+        d.n = run_n
+        asked = rt3d.rt3d_conv3d_workspace_size(d, info)
+        for pitch, off in ((0, 0), (-(-c_in // 8) * 8, 0), (-(-c_in // 8) * 8 + 16, 8), (c_in + 1, 1)):
+            d.x_c_total, d.x_c_off = pitch, off
+            want = rt3d.rt3d_conv3d_launch_info(d, info)
+            got = rt3d.rt3d_conv3d_launch_info(d, info, asked)
+            assert bytes(want) == bytes(got), (c_in, c_out, thw, k, n, run_n, pitch)
+            grew += want.kernel == rt3d.KERNELS.index("wide") and want.splits > 1
+    assert grew > 5   # (split wide launches were among them)
