@@ -58,6 +58,12 @@ int tune(const char *key) {
   return -1;
 }
 
+// The overrides of one forward call: one look at the environment, not one a key.
+struct Tune {
+  const bool on = std::getenv("RT3D_TUNE") != nullptr;
+  int operator()(const char *key) const { return on ? tune(key) : -1; }
+};
+
 uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 
 int out_len(int in, int k, int s, int p) {
@@ -1314,7 +1320,6 @@ struct WideLaunch {
   int wm = 0, wk = 0;      // waves along the filters, parts of the reduction
   int splits = 1;          // channel-chunk splits across workgroups
   uint64_t ws_bytes = 0;
-  int order = 0;
   long wgs = 0;            // workgroups that run at once
   double cycles = 0;       // modelled time
 };
@@ -1329,29 +1334,53 @@ constexpr double kWideLoad = 5.8, kWideLoadFree = 4817, kWideChunk = 670, kWideS
 // kernel runs in one (small eager calls are bound by launches: 64->64 3x3x3 on
 // 4x14x14 took 10.5 us unsplit on the item kernel and 13.5 split on this one).
 constexpr double kWideSecondLaunch = 10000;
+constexpr double kNoLimit = 1e300;
 constexpr double kWideReduceStart = 4700, kWidePartialBytes = 0.63;
 
-// The best launch shape of a wide plan, by a time model in cycles.  A
-// workgroup per CU walks its tiles one after the other; a tile is its chunks
-// (K-steps, or the loads of the next chunk where those take longer, and a
-// barrier) and its epilogue, a launch adds its start and the first chunk's
-// loads, splits add partial sums and their reduction.  The constants were
-// fitted to 110 layers of the C3D, R(2+1)D and S3D stacks at batch 1 to 32
-// (mean error 5.5%).
+// The best launch shape of a wide plan, by a time model in cycles; fm = 0 when
+// none takes at most `limit`.  A workgroup per CU walks its tiles one after the
+// other; a tile is its chunks (K-steps, or the loads of the next chunk where
+// those take longer, and a barrier) and its epilogue, a launch adds its start
+// and the first chunk's loads, splits add partial sums and their reduction.
+// The constants were fitted to 110 layers of the C3D, R(2+1)D and S3D stacks at
+// batch 1 to 32 (mean error 5.5%).
+//
+// Every forward call runs this search, and small layers are bound by the host:
+// the split counts are listed once for all wave shapes, and a wave shape or the
+// rest of its split counts is passed over once its least time (one round, or
+// all chunks spread over the CUs) reaches the best so far or the limit.
 WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cus, int want_splits,
-                     int want_fm, int want_wm, double second_launch = 0) {
+                     int want_fm, int want_wm, double second_launch, double limit) {
   WideLaunch best;
   best.wgs = cus;
   const long bricks = static_cast<long>(g.n) * ((g.to + wp.bt - 1) / wp.bt) *
                       ((g.ho + wp.bh - 1) / wp.bh) * ((g.wo + wp.bw - 1) / wp.bw);
+  if (bricks >= (1L << 24)) return best;
   const int c16_total = (g.c_in + 15) / 16, nch = (c16_total + wp.c16 - 1) / wp.c16;
   const uint64_t per_split =
       static_cast<uint64_t>(g.n) * g.to * g.ho * g.wo * ((g.c_out + 3) / 4 * 4) * 4;
   const int rows32 = (g.c_out + 31) / 32;
   const double rows = static_cast<double>((wp.bt - 1) * g.st + g.kt) * ((wp.bh - 1) * g.sh + g.kh) *
                       ((wp.bw - 1) * g.sw + g.kw);
-  const double load = kWideLoad * rows * wp.c16;
-  double best_t = -1;
+  const double load = kWideLoad * rows * wp.c16, base = kWideStart + load;
+  const double split_base = second_launch + kWideReduceStart;
+  const double split_each = kWidePartialBytes / 1000 * 2.0 * static_cast<double>(per_split);
+  // Chunks per workgroup and the split count that makes, each count once
+  // (ceil(nch / k) takes at most 2 sqrt(nch) + 1 values, nch < 4096).
+  struct { int per, s; } share[160];
+  int shares = 0;
+  const int want = want_splits > 0 ? std::min(nch, want_splits) : 0;
+  for (int per = nch; per >= 1 && shares < 160;) {
+    const int s = (nch + per - 1) / per;
+    if (s > 1 && (per_split * s > ws_cap || (want && s > want))) break;
+    share[shares++] = {per, s};
+    // the next smaller chunk count that changes the split count
+    const int next = (nch + s) / (s + 1);
+    per = next < per ? next : per - 1;
+  }
+  const double spread = static_cast<double>(bricks) * nch / static_cast<double>(cus);
+  const uint32_t cu = static_cast<uint32_t>(cus);
+  double best_t = limit;
   for (int fm = 1; fm <= 2; ++fm) {
     if (want_fm > 0 && want_fm != fm) continue;
     const int tiles = (rows32 + fm - 1) / fm;
@@ -1363,42 +1392,29 @@ WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cu
       if (chunk_steps > kWideSteps) continue;
       const long ntg = (tiles + wm - 1) / wm;
       const double chunk = std::max(chunk_steps * kWideStep[fm], load - kWideLoadFree) + kWideChunk;
-      for (int per = nch; per >= 1;) {   // chunks per workgroup; s = ceil(nch / per) splits
-        const int s = (nch + per - 1) / per;
-        if (s > 1 && per_split * s > ws_cap) break;
-        const int want = want_splits > 0 ? std::min(nch, want_splits) : 0;
+      // (0.999999: the bound rounds differently from the times below)
+      const double least = 0.999999 * (std::max(spread * static_cast<double>(ntg), 1.0) * chunk + kWideTile[fm] + base);
+      if (!want && least >= best_t) continue;
+      for (int k = 0; k < shares; ++k) {
+        const int s = share[k].s;
         const long n = bricks * ntg * s;
         if (n >= (1L << 24)) break;
-        if (!want || s <= want) {
-          double t = static_cast<double>((n + cus - 1) / cus) * (per * chunk + kWideTile[fm]) + kWideStart + load;
-          if (s > 1) t += second_launch + kWideReduceStart + kWidePartialBytes / 1000 * 2.0 * static_cast<double>(s * per_split);
-          if (best_t < 0 || t < best_t || (want && s > best.splits)) {
-            best_t = t;
-            best.fm = fm;
-            best.wm = wm;
-            best.wk = wk;
-            best.splits = s;
-            best.ws_bytes = s > 1 ? per_split * s : 0;
-            best.cycles = t;
-          }
+        const double split = s > 1 ? split_base + split_each * s : 0.0;
+        if (!want && least + 0.999999 * split >= best_t) break;
+        const double t = ((static_cast<uint32_t>(n) + cu - 1) / cu) * (share[k].per * chunk + kWideTile[fm]) + base + split;
+        if (t < best_t || (want && s > best.splits)) {
+          best_t = t;
+          best.fm = fm;
+          best.wm = wm;
+          best.wk = wk;
+          best.splits = s;
+          best.ws_bytes = s > 1 ? per_split * s : 0;
+          best.cycles = t;
         }
-        if (per == 1) break;
-        // the next smaller chunk count that changes the split count
-        const int next = (nch + s) / (s + 1);
-        per = next < per ? next : per - 1;
       }
     }
   }
   return best;
-}
-
-// A lower bound of best_wide's cycles: one tile of one chunk, its reduction
-// cut four ways, after the start and the first loads.
-double least_wide(const Geom &g, const WidePlan &wp) {
-  const double rows = static_cast<double>((wp.bt - 1) * g.st + g.kt) * ((wp.bh - 1) * g.sh + g.kh) *
-                      ((wp.bw - 1) * g.sw + g.kw);
-  return kWideStart + kWideLoad * rows * wp.c16 + kWideChunk + kWideTile[1] +
-         (g.ks * wp.c16 + 3) / 4 * kWideStep[1];
 }
 
 // Brick, halo pitches and chunk width of the wide kernel for this batch
@@ -1458,9 +1474,10 @@ WidePlan wide_tiling(const Geom &g, int fn) {
       wp.fn = static_cast<uint8_t>(fn);
       Geom one = g;
       one.n = std::max(g.n, 1);
-      const WideLaunch L = best_wide(one, wp, kScratchBytes, 256, 0, 0, 0);
+      const double slow = 1.0 + 0.04 * (conf - 1.0);
+      const WideLaunch L = best_wide(one, wp, kScratchBytes, 256, 0, 0, 0, 0, best_t < 0 ? kNoLimit : 1.000001 * best_t / slow);
       if (L.fm == 0) continue;
-      const double t = L.cycles * (1.0 + 0.04 * (conf - 1.0));
+      const double t = L.cycles * slow;
       if (best_t < 0 || t < best_t) {
         best_t = t;
         best = wp;
@@ -1918,13 +1935,12 @@ int cached_small_resident(const ConvArgs &a, int dtype, int mfw) {
   return n;
 }
 
-Launch plan_launch(const rt3d_conv3d_desc *d, const Plan &p, uint32_t variant, uint64_t ws_cap,
-                   uint64_t a_bytes) {
-  const Geom g = geom_of(d);
+Launch plan_launch(const rt3d_conv3d_desc *d, const Geom &g, const Plan &p, uint32_t variant, uint64_t ws_cap,
+                   const Tune &tuned) {
   const Tiling &tl = p.tiling;
   const long bricks = static_cast<long>(g.n) * ((g.to + tl.bt - 1) / tl.bt) *
                       ((g.ho + tl.bh - 1) / tl.bh) * ((g.wo + tl.bw - 1) / tl.bw);
-  Launch L{4, 1, 0, 0, 0};
+  Launch L{4, 1, 0, 0};
   if (variant == kVarSmallDense16 || variant == kVarSmallKgs16) return L;  // one chunk, no split
   const long ntg = (p.wave_tiles + L.wpw - 1) / L.wpw;
   const long wgs = bricks * ntg;
@@ -1941,20 +1957,13 @@ Launch plan_launch(const rt3d_conv3d_desc *d, const Plan &p, uint32_t variant, u
   const double chunk_steps = p.tile_steps > 0 ? static_cast<double>(p.tile_steps) / tl.nchunks : 24.0;
   const SplitModel model(g, tl, p.mfw, chunk_steps, variant, wgs, per_cu_split, per_cu_whole, device_cus());
   int splits = model.best();
-  if (tune("splits") > 0) splits = std::max(1, std::min(tl.nchunks, tune("splits")));
+  if (tuned("splits") > 0) splits = std::max(1, std::min(tl.nchunks, tuned("splits")));
   const long total_vox = static_cast<long>(g.n) * g.to * g.ho * g.wo;
   const uint64_t per_split = static_cast<uint64_t>(total_vox) * ((g.c_out + 3) / 4 * 4) * 4;
   while (splits > 1 && per_split * splits > ws_cap) --splits;
   L.splits = splits;
   L.cycles = model.cycles(splits);   // of the launch that is made: the workspace may have cut the splits
   L.ws_bytes = splits > 1 ? per_split * splits : 0;
-  const double a_unit = static_cast<double>(a_bytes) / (static_cast<double>(ntg) * splits);
-  const double x_unit = static_cast<double>(tl.ht) * tl.hh * tl.hw * tl.cc * g.es * tl.nchunks / splits;
-  L.order = xcd_fill_bytes(bricks, ntg, splits, 1, a_unit, x_unit) <
-                    xcd_fill_bytes(bricks, ntg, splits, 0, a_unit, x_unit)
-                ? 1
-                : 0;
-  if (tune("wg_order") >= 0) L.order = tune("wg_order") ? 1 : 0;
   return L;
 }
 
@@ -1967,44 +1976,28 @@ WidePlan wide_plan_of(const rt3d_pack_info *info) {
 // The wide kernel's launch for this call, fm = 0 when the call runs on the
 // item kernel: no wide layout in the blob, an input pitch or offset that is
 // not a multiple of 8 channels (the staging loads whole 16-byte pieces), a
-// blob that ends less than kWideTail bytes behind the weights, a batch item of 4 GiB or more (32-bit halo offsets), or an item-kernel launch
-// that is modelled faster.  The item kernel's model was fitted like the wide
+// blob that ends less than kWideTail bytes behind the weights, a batch item of
+// 4 GiB or more (32-bit halo offsets), or an item-kernel launch that is modelled
+// faster.  The item kernel's model was fitted like the wide
 // one's (its own cycles x 0.73 plus 1.06 us per million outputs, 10% mean
 // error); the 5% margin keeps the item kernel where the two are close.
-WideLaunch plan_wide(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, uint64_t ws_cap,
-                     const Launch &item_launch) {
+WideLaunch plan_wide(const rt3d_conv3d_desc *d, const Geom &g, const rt3d_pack_info *info, uint64_t ws_cap,
+                     const Launch &item_launch, const Tune &tuned) {
   const WidePlan wp = wide_plan_of(info);
   WideLaunch none;
   if (wp.a_off == 0 || wp.rgb) return none;
   const int x_pitch = d->x_c_total != 0 ? d->x_c_total : d->c_in;
   if (x_pitch % 8 != 0 || d->x_c_off % 8 != 0) return none;
-  const Geom g = geom_of(d);
   if (info->packed_bytes < wp.a_off + wide_weight_bytes(g) + kWideTail) return none;
   if (static_cast<double>(g.t) * g.h * g.w * x_pitch * 2 >= 4.29e9) return none;
-  const bool tuned = std::getenv("RT3D_TUNE") != nullptr;   // (one look at the environment a call)
-  auto want = [&](const char *key) { return tuned ? tune(key) : -1; };
   const double outputs = static_cast<double>(g.n) * g.to * g.ho * g.wo * g.c_out;
   const double item = 0.73 * item_launch.cycles + 2383e-6 * outputs;
-  auto item_wins = [&](double wide) { return want("wide") != 1 && item < 1.05 * wide; };
-  // A small layer that the item kernel wins by the bound alone is spared the
-  // search: its call is bound by the host.  (0.999: the bound's rounding)
-  if (item_wins(0.999 * least_wide(g, wp))) return none;
-  WideLaunch L = best_wide(g, wp, std::min<uint64_t>(ws_cap, kScratchBytes), device_cus(),
-                           want("splits"), want("wide_fm"), want("wide_wm"),
-                           item_launch.splits > 1 ? 0 : kWideSecondLaunch);
-  if (L.fm == 0 || item_wins(L.cycles)) return none;
-  const long bricks = static_cast<long>(g.n) * ((g.to + wp.bt - 1) / wp.bt) *
-                      ((g.ho + wp.bh - 1) / wp.bh) * ((g.wo + wp.bw - 1) / wp.bw);
-  const int c16_total = (g.c_in + 15) / 16, rows32 = (g.c_out + 31) / 32;
-  const long ntg = ((rows32 + L.fm - 1) / L.fm + L.wm - 1) / L.wm;
-  const double a_unit = static_cast<double>(rows32) * 1024 * g.ks * c16_total / (static_cast<double>(ntg) * L.splits);
-  const double x_unit = static_cast<double>(wp.hpp) * ((wp.bt - 1) * g.st + g.kt) * c16_total * 32.0 / L.splits;
-  L.order = xcd_fill_bytes(bricks, ntg, L.splits, 1, a_unit, x_unit) <
-                    xcd_fill_bytes(bricks, ntg, L.splits, 0, a_unit, x_unit)
-                ? 1
-                : 0;
-  if (tune("wg_order") >= 0) L.order = tune("wg_order") ? 1 : 0;
-  return L;
+  // (a tuning switch may ask for shapes that the model would not take)
+  const bool free_choice = tuned("wide") != 1;
+  const double limit = tuned.on ? kNoLimit : 1.000001 * item / 1.05;
+  const WideLaunch L = best_wide(g, wp, std::min<uint64_t>(ws_cap, kScratchBytes), device_cus(), tuned("splits"),
+                                 tuned("wide_fm"), tuned("wide_wm"), item_launch.splits > 1 ? 0 : kWideSecondLaunch, limit);
+  return L.fm == 0 || (free_choice && item < 1.05 * L.cycles) ? none : L;
 }
 
 // Bytes of the item kernel's weight section (the wide section, when there is
@@ -2014,12 +2007,39 @@ uint64_t item_bytes(const rt3d_pack_info *info, const Plan &p) {
   return (wp.a_off != 0 ? wp.a_off : info->packed_bytes) - p.a_off;
 }
 
+// ConvArgs::order of a launch: the one whose XCDs read the fewer bytes.
+int order_of(long bricks, long ntg, int splits, double a_bytes, double x_bytes, const Tune &tuned) {
+  if (tuned("wg_order") >= 0) return tuned("wg_order") ? 1 : 0;
+  const double a_unit = a_bytes / (static_cast<double>(ntg) * splits), x_unit = x_bytes / splits;
+  return xcd_fill_bytes(bricks, ntg, splits, 1, a_unit, x_unit) < xcd_fill_bytes(bricks, ntg, splits, 0, a_unit, x_unit)
+             ? 1
+             : 0;
+}
+
+int item_order(const Geom &g, const rt3d_pack_info *info, const Plan &p, const Launch &L, const Tune &tuned) {
+  if (info->variant == kVarSmallDense16 || info->variant == kVarSmallKgs16) return 0;
+  const Tiling &tl = p.tiling;
+  const long bricks = static_cast<long>(g.n) * ((g.to + tl.bt - 1) / tl.bt) *
+                      ((g.ho + tl.bh - 1) / tl.bh) * ((g.wo + tl.bw - 1) / tl.bw);
+  return order_of(bricks, (p.wave_tiles + L.wpw - 1) / L.wpw, L.splits, static_cast<double>(item_bytes(info, p)),
+                  static_cast<double>(tl.ht) * tl.hh * tl.hw * tl.cc * g.es * tl.nchunks, tuned);
+}
+
+int wide_order(const Geom &g, const WidePlan &wp, const WideLaunch &L, const Tune &tuned) {
+  const long bricks = static_cast<long>(g.n) * ((g.to + wp.bt - 1) / wp.bt) *
+                      ((g.ho + wp.bh - 1) / wp.bh) * ((g.wo + wp.bw - 1) / wp.bw);
+  const int c16_total = (g.c_in + 15) / 16, rows32 = (g.c_out + 31) / 32;
+  return order_of(bricks, ((rows32 + L.fm - 1) / L.fm + L.wm - 1) / L.wm, L.splits,
+                  static_cast<double>(rows32) * 1024 * g.ks * c16_total,
+                  static_cast<double>(wp.hpp) * ((wp.bt - 1) * g.st + g.kt) * c16_total * 32.0, tuned);
+}
+
 // Layers with up to 4 input channels: the RGB kernel, except where a residual
 // is added or an output voxel's filters are not whole 16-byte words (the
 // small-channel kernel).
-bool takes_rgb(const rt3d_conv3d_desc *d, const WidePlan &wp) {
+bool takes_rgb(const rt3d_conv3d_desc *d, const WidePlan &wp, const Tune &tuned) {
   const int y_pitch = d->y_c_total != 0 ? d->y_c_total : d->c_out;
-  return wp.a_off != 0 && wp.rgb && !(d->flags & RT3D_RESIDUAL) && tune("wide") != 0 &&
+  return wp.a_off != 0 && wp.rgb && !(d->flags & RT3D_RESIDUAL) && tuned("wide") != 0 &&
          (d->c_out | y_pitch | d->y_c_off) % 8 == 0;
 }
 
@@ -2040,10 +2060,11 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
     return fail(RT3D_ERR_INVALID_ARG, "device pointers must be 16-byte aligned");
   Plan p;
   std::memcpy(&p, info->plan, sizeof(p));
-  const Launch launch = plan_launch(d, p, info->variant, workspace ? ws_bytes : 0, item_bytes(info, p));
-  const WidePlan wp = wide_plan_of(info);
-  const WideLaunch wl = plan_wide(d, info, workspace ? ws_bytes : 0, launch);
+  const Tune tuned;
   const Geom g = geom_of(d);
+  const Launch launch = plan_launch(d, g, p, info->variant, workspace ? ws_bytes : 0, tuned);
+  const WidePlan wp = wide_plan_of(info);
+  const WideLaunch wl = plan_wide(d, g, info, workspace ? ws_bytes : 0, launch, tuned);
   const Tiling &tl = p.tiling;
   const uint8_t *b = static_cast<const uint8_t *>(blob);
   ConvArgs a{};
@@ -2084,7 +2105,7 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   a.pto = g.pto; a.pho = g.pho; a.pwo = g.pwo;
   a.c_wg = a.wpw * 16 * p.mfw;
   a.tile_row = a.c_wg * 4 + 16;  // +16 bytes: slot rows start on different banks
-  a.order = launch.order;
+  a.order = wl.fm > 0 ? wide_order(g, wp, wl, tuned) : item_order(g, info, p, launch, tuned);
   a.nbricks = static_cast<int32_t>(static_cast<long>(a.n) * a.nbt * a.nbh * a.nbw);
   a.ntg = (a.wave_tiles + a.wpw - 1) / a.wpw;
   a.grid = 0;  // one workgroup per tile
@@ -2100,7 +2121,7 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   if (static_cast<long>(a.n) * a.nbt * a.nbh * a.nbw * a.ntg * a.splits >= (1L << 24))
     return fail(RT3D_ERR_UNSUPPORTED, "layer needs 2^24 or more workgroups");
   int e;
-  if (takes_rgb(d, wp)) {
+  if (takes_rgb(d, wp, tuned)) {
     const RgbShape r = rgb_shape(g);
     WideArgs ra{};
     static_cast<ConvArgs &>(ra) = a;
@@ -2145,7 +2166,6 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
     wa.kh = g.kh; wa.kw = g.kw; wa.ks = g.ks;
     wa.stot = g.ks * wa.c16_total;
     wa.splits = wl.splits;
-    wa.order = wl.order;
     wa.wave_tiles = ((g.c_out + 31) / 32 + wl.fm - 1) / wl.fm;
     wa.ntg = (wa.wave_tiles + wl.wm - 1) / wl.wm;
     wa.nbricks = static_cast<int32_t>(static_cast<long>(g.n) * wa.nbt * wa.nbh * wa.nbw);
@@ -2380,15 +2400,17 @@ rt3d_status rt3d_conv3d_workspace_size(const rt3d_conv3d_desc *d, const rt3d_pac
     return fail(RT3D_ERR_BLOB_MISMATCH, "info does not belong to this layer description");
   Plan p;
   std::memcpy(&p, info->plan, sizeof(p));
-  const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, item_bytes(info, p));
+  const Tune tuned;
+  const Geom g = geom_of(d);
+  const Launch L = plan_launch(d, g, p, info->variant, UINT64_MAX, tuned);
   // Enough for either kernel.  A desc that names no input pitch stands for
   // every pitch: a ragged channel count is counted on a pitch of whole 16-byte
   // pieces too, on which the wide kernel can run.
-  *bytes = std::max(L.ws_bytes, plan_wide(d, info, UINT64_MAX, L).ws_bytes);
+  *bytes = std::max(L.ws_bytes, plan_wide(d, g, info, UINT64_MAX, L, tuned).ws_bytes);
   if (d->x_c_total == 0 && d->c_in % 8 != 0) {
     rt3d_conv3d_desc padded = *d;
     padded.x_c_total = (d->c_in + 7) / 8 * 8;
-    *bytes = std::max(*bytes, plan_wide(&padded, info, UINT64_MAX, L).ws_bytes);
+    *bytes = std::max(*bytes, plan_wide(&padded, g, info, UINT64_MAX, L, tuned).ws_bytes);
   }
   return ok();
 }
@@ -2403,16 +2425,19 @@ rt3d_status rt3d_conv3d_launch_info(const rt3d_conv3d_desc *d, const rt3d_pack_i
   Plan p;
   std::memcpy(&p, info->plan, sizeof(p));
   const WidePlan wp = wide_plan_of(info);
-  const Launch L = plan_launch(d, p, info->variant, workspace_bytes, item_bytes(info, p));
-  const WideLaunch W = plan_wide(d, info, workspace_bytes, L);
-  if (takes_rgb(d, wp))
+  const Tune tuned;
+  const Geom g = geom_of(d);
+  const Launch L = plan_launch(d, g, p, info->variant, workspace_bytes, tuned);
+  const WideLaunch W = plan_wide(d, g, info, workspace_bytes, L, tuned);
+  if (takes_rgb(d, wp, tuned))
     *out = {RT3D_KERNEL_RGB, 4, 4, 32, d->c_in, 64, 1, 1, 1, 0, 0};
   else if (W.fm > 0)
-    *out = {RT3D_KERNEL_WIDE, wp.bt, wp.bh, wp.bw, wp.c16 * 16, 32 * W.fm, W.wm, W.wk, W.splits, W.order, W.ws_bytes};
+    *out = {RT3D_KERNEL_WIDE, wp.bt, wp.bh, wp.bw, wp.c16 * 16, 32 * W.fm, W.wm, W.wk, W.splits, wide_order(g, wp, W, tuned), W.ws_bytes};
   else
     *out = {info->variant == kVarSmallDense16 || info->variant == kVarSmallKgs16 ? RT3D_KERNEL_SMALL
                                                                                  : RT3D_KERNEL_ITEM,
-            p.tiling.bt, p.tiling.bh, p.tiling.bw, p.tiling.cc, 16 * p.mfw, L.wpw, 1, L.splits, L.order, L.ws_bytes};
+            p.tiling.bt, p.tiling.bh, p.tiling.bw, p.tiling.cc, 16 * p.mfw, L.wpw, 1, L.splits,
+            item_order(g, info, p, L, tuned), L.ws_bytes};
   return ok();
 }
 
@@ -2435,9 +2460,11 @@ rt3d_status rt3d_kgs_conv3d_fwd_noalloc(const rt3d_conv3d_desc *d, const rt3d_pa
   std::memcpy(&p, info->plan, sizeof(p));
   // The split count a caller workspace of any size would get: the launch is
   // then the one rt3d_kgs_conv3d_fwd makes with that workspace.
-  const Launch L = plan_launch(d, p, info->variant, UINT64_MAX, item_bytes(info, p));
+  const Tune tuned;
+  const Geom g = geom_of(d);
+  const Launch L = plan_launch(d, g, p, info->variant, UINT64_MAX, tuned);
   const uint64_t need =
-      std::max(L.ws_bytes, plan_wide(d, info, UINT64_MAX, L).ws_bytes);
+      std::max(L.ws_bytes, plan_wide(d, g, info, UINT64_MAX, L, tuned).ws_bytes);
   if (need > kScratchBytes)
     return fail(RT3D_ERR_UNSUPPORTED,
                 "this launch needs %llu bytes of split-K scratch; the no-allocation entry point "

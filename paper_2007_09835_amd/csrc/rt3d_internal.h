@@ -177,7 +177,6 @@ struct Launch {
   int wpw;
   int splits;
   uint64_t ws_bytes;
-  int order;  // ConvArgs::order
   double cycles;  // modelled time
 };
 

@@ -84,3 +84,22 @@ def test_workspace_covers_every_input_pitch():
             assert bytes(want) == bytes(got), (c_in, c_out, thw, k, n, run_n, pitch)
             grew += want.kernel == rt3d.KERNELS.index("wide") and want.splits > 1
     assert grew > 5   # (split wide launches were among them)
+
+
+def test_tuning_switches_do_not_bend_the_search(monkeypatch):
+    """The search passes over shapes that its bound rules out: a call that a
+    switch forces onto the wide kernel takes the shape of the free search."""
+    wide = rt3d.KERNELS.index("wide")
+    seen = 0
+    for c_in, c_out, thw, k, n in shapes(60, 5):
+        d, info = pack(c_in, c_out, thw, k, n)
+        for ws in (0, 1 << 20, 2 ** 64 - 1):
+            free = rt3d.rt3d_conv3d_launch_info(d, info, ws)
+            monkeypatch.setenv("RT3D_TUNE", "wide=1")
+            forced = rt3d.rt3d_conv3d_launch_info(d, info, ws)
+            monkeypatch.delenv("RT3D_TUNE")
+            assert forced.kernel == wide
+            if free.kernel == wide:
+                assert bytes(free) == bytes(forced), (c_in, c_out, thw, k, n, ws)
+                seen += 1
+    assert seen > 20
