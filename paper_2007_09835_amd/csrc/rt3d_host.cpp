@@ -401,7 +401,8 @@ struct Layout {
   std::vector<uint32_t> step_ptr, item_ptr, items, keep;
   std::vector<uint8_t> a;  // operand stream, raw element bytes
   WidePlan wide{};         // c16 > 0: the blob also holds the wide layout
-  std::vector<uint8_t> wide_a;
+  uint64_t wide_bytes = 0;
+  uint64_t a_sized = 0;    // bytes of an operand stream that is sized, not built
 };
 
 // Element (filter m, channel c, position pos) of the dense weights, or zero
@@ -807,6 +808,7 @@ long union_steps(const Geom &g, const Tiling &tl, const Mask4 &m4, int mfw) {
 // K-steps; the keep section then maps each wave tile's block slots to layer
 // blocks.
 
+// (w may be null: the stream is then sized only.)
 void build_items_layout(const Geom &g, const Tiling &tl, const uint8_t *w, const Mask4 *m4,
                         Layout &L, bool small, int mfw) {
   const bool f32 = g.es == 4;
@@ -875,8 +877,14 @@ void build_items_layout(const Geom &g, const Tiling &tl, const uint8_t *w, const
           for (int e = 0; e < ips; ++e)
             L.items.push_back(si[e].ql < 0 ? 0u : item_offset(g, tl, si[e].ql, si[e].pos));
         // A operand for this step, MFMA lane order.
+        ++step;
+        const size_t bytes = static_cast<size_t>(mfw) * 64 * epl * g.es;
+        if (!w) {
+          L.a_sized += bytes;
+          continue;
+        }
         const size_t base = L.a.size();
-        L.a.resize(base + static_cast<size_t>(mfw) * 64 * epl * g.es);
+        L.a.resize(base + bytes);
         uint8_t *dst = L.a.data() + base;
         for (int i = 0; i < mfw; ++i)
           for (int lane = 0; lane < 64; ++lane)
@@ -895,7 +903,6 @@ void build_items_layout(const Geom &g, const Tiling &tl, const uint8_t *w, const
                 src.copy(out, m, c, it.pos);
               }
             }
-        ++step;
       }
     }
     L.step_ptr[static_cast<size_t>(wt) * (tl.nchunks + 1) + tl.nchunks] = step;
@@ -1299,16 +1306,13 @@ void build_exact_f32_layout(const Geom &g, const Tiling &tl, const uint8_t *w, c
 // Cycles a 16-lane set of a ds_read_b128 takes beyond one: the most distinct
 // rows (of an odd multiple of 16 bytes) that share a bank group, over the two
 // sets of every 32-slot fragment, averaged.
-double wide_conflict(const Geom &g, int bt, int bh, int bw, int hwp, int hpp, int slots) {
+// slot_t/h/w: halo position of each of the brick's voxel slots.
+double wide_conflict(const int *slot_t, const int *slot_h, const int *slot_w, int voxels, int hwp, int hpp, int slots) {
   int total = 0;
   for (int f = 0; f < slots / 16; ++f) {
     int hits[16] = {0}, worst = 1;
-    for (int n = 0; n < 16; ++n) {
-      const int s = 16 * f + n, tt = s / (bh * bw), hh = (s / bw) % bh, ww = s % bw;
-      if (tt >= bt) continue;
-      const int r = (tt * g.st) * hpp + (hh * g.sh) * hwp + ww * g.sw;
-      worst = std::max(worst, ++hits[r & 15]);
-    }
+    for (int s = 16 * f; s < std::min(16 * f + 16, voxels); ++s)
+      worst = std::max(worst, ++hits[(slot_t[s] * hpp + slot_h[s] * hwp + slot_w[s]) & 15]);
     total += worst;
   }
   return total / (slots / 16.0);
@@ -1442,16 +1446,46 @@ WidePlan wide_tiling(const Geom &g, int fn) {
   each_brick([&](int bt, int bh, int bw, double nb) {
     if (nb <= 1.15 * min_nb) min_rows = min_rows < 0 ? rows_of(bt, bh, bw) : std::min(min_rows, rows_of(bt, bh, bw));
   });
-  double best_t = -1;
+  Geom one = g;
+  one.n = std::max(g.n, 1);
+  double best_t = kNoLimit;
   each_brick([&](int bt, int bh, int bw, double nb) {
     if (nb > 1.15 * min_nb || rows_of(bt, bh, bw) > 1.6 * min_rows) return;
     const int ht = (bt - 1) * g.st + g.kt, hh = (bh - 1) * g.sh + g.kh, hw = (bw - 1) * g.sw + g.kw;
     if (ht > 511 || hh > 511 || hw > 511) return;   // 9 bits each in the stage table
+    auto fits = [&](long rows, int c16) {
+      const long row = c16 * 32 + 16;
+      return 2 * rows * row + kWideFixedLds <= kWideLds && rows * (row / 16) <= kWidePieces * 256;
+    };
+    WidePlan wp{};
+    wp.bt = static_cast<uint8_t>(bt);
+    wp.bh = static_cast<uint8_t>(bh);
+    wp.bw = static_cast<uint8_t>(bw);
+    wp.fn = static_cast<uint8_t>(fn);
+    // Times without conflicts first: the pitches are searched for bricks that
+    // can still win only.  (1.000001: the factor below may round to less than 1)
+    double cycles[9];
+    int widest = 0;
+    for (int c16 = 1; c16 <= std::min(8, c16_total) && fits(static_cast<long>(ht) * hh * hw, c16); ++c16) {
+      wp.c16 = static_cast<uint8_t>(c16);
+      const WideLaunch L = best_wide(one, wp, kScratchBytes, 256, 0, 0, 0, 0, 1.000001 * best_t);
+      cycles[c16] = L.fm == 0 ? kNoLimit : L.cycles;
+      if (L.fm != 0) widest = c16;
+    }
+    if (widest == 0) return;
+    int slot_t[128], slot_h[128], slot_w[128], voxels = 0;
+    for (int t = 0; t < bt; ++t)
+      for (int h = 0; h < bh; ++h)
+        for (int w = 0; w < bw; ++w, ++voxels) {
+          slot_t[voxels] = t * g.st;
+          slot_h[voxels] = h * g.sh;
+          slot_w[voxels] = w * g.sw;
+        }
     double conf = -1;
     int hwp = hw, hpp = hh * hw;
     for (int pw = 0; pw < 4; ++pw)
       for (int pp = 0; pp < 4; ++pp) {
-        const double c = wide_conflict(g, bt, bh, bw, hw + pw, hh * (hw + pw) + pp, slots) +
+        const double c = wide_conflict(slot_t, slot_h, slot_w, voxels, hw + pw, hh * (hw + pw) + pp, slots) +
                          0.3 * (static_cast<double>(ht) * (hh * (hw + pw) + pp) / (static_cast<double>(ht) * hh * hw) - 1);
         if (conf < 0 || c < conf) {
           conf = c;
@@ -1461,26 +1495,14 @@ WidePlan wide_tiling(const Geom &g, int fn) {
       }
     const long rows = static_cast<long>(ht) * hpp;
     if (hpp > 65535 || rows > 4096) return;
-    for (int c16 = 1; c16 <= std::min(8, c16_total); ++c16) {
-      const long row = c16 * 32 + 16;
-      if (2 * rows * row + kWideFixedLds > kWideLds || rows * (row / 16) > 11 * 256) break;
-      WidePlan wp{};
-      wp.bt = static_cast<uint8_t>(bt);
-      wp.bh = static_cast<uint8_t>(bh);
-      wp.bw = static_cast<uint8_t>(bw);
-      wp.c16 = static_cast<uint8_t>(c16);
-      wp.hwp = static_cast<uint16_t>(hwp);
-      wp.hpp = static_cast<uint16_t>(hpp);
-      wp.fn = static_cast<uint8_t>(fn);
-      Geom one = g;
-      one.n = std::max(g.n, 1);
-      const double slow = 1.0 + 0.04 * (conf - 1.0);
-      const WideLaunch L = best_wide(one, wp, kScratchBytes, 256, 0, 0, 0, 0, best_t < 0 ? kNoLimit : 1.000001 * best_t / slow);
-      if (L.fm == 0) continue;
-      const double t = L.cycles * slow;
-      if (best_t < 0 || t < best_t) {
+    wp.hwp = static_cast<uint16_t>(hwp);
+    wp.hpp = static_cast<uint16_t>(hpp);
+    for (int c16 = 1; c16 <= widest && fits(rows, c16); ++c16) {
+      const double t = cycles[c16] * (1.0 + 0.04 * (conf - 1.0));
+      if (t < best_t) {
         best_t = t;
         best = wp;
+        best.c16 = static_cast<uint8_t>(c16);
       }
     }
   });
@@ -1507,12 +1529,12 @@ RgbShape rgb_shape(const Geom &g) {
 
 // The RGB kernel's weights: step (kernel row, tap group s), lane (m, half),
 // element e = channel e % 4 of tap 4 s + 2 half + e / 4.
-void build_rgb_layout(const Geom &g, const uint8_t *w, const Mask4 *m4, std::vector<uint8_t> &out) {
+// out holds zeros.
+void build_rgb_layout(const Geom &g, const uint8_t *w, const Mask4 *m4, uint8_t *out) {
   const RgbShape r = rgb_shape(g);
-  const int tiles = (g.c_out + 63) / 64, s4 = (g.kw + 3) / 4;
-  out.assign(static_cast<size_t>(tiles) * r.steps * 2048, 0);
+  const int s4 = (g.kw + 3) / 4;
   const uint16_t *src = reinterpret_cast<const uint16_t *>(w);
-  uint16_t *dst = reinterpret_cast<uint16_t *>(out.data());
+  uint16_t *dst = reinterpret_cast<uint16_t *>(out);
   for (int m = 0; m < g.c_out; ++m)
     for (int c = 0; c < g.c_in; ++c)
       for (int pos = 0; pos < g.ks; ++pos) {
@@ -1526,7 +1548,7 @@ void build_rgb_layout(const Geom &g, const uint8_t *w, const Mask4 *m4, std::vec
 
 // Does a pack write the wide layout?  16-bit layers off the small-channel
 // kernel, unless a tuning switch names an item-kernel layout.
-bool wide_wanted(const Geom &g, bool small, const Mask4 *m4) {
+bool wide_wanted(const Geom &g, bool small) {
   if (g.es != 2 || small || g.c_in < 16) return false;
   const int v = tune("wide");
   if (v == 0) return false;
@@ -1534,7 +1556,6 @@ bool wide_wanted(const Geom &g, bool small, const Mask4 *m4) {
     if (tune(key) >= 0) return false;
   // the weight section is addressed with 31 bits
   if (static_cast<double>((g.c_out + 63) / 64 * 64) * g.ks * ((g.c_in + 15) / 16 * 16) * 2 >= 2.1e9) return false;
-  (void)m4;
   return true;
 }
 
@@ -1543,13 +1564,18 @@ uint64_t wide_weight_bytes(const Geom &g) {
   return static_cast<uint64_t>(((g.c_out + 31) / 32 + 1) / 2 * 2) * g.ks * ((g.c_in + 15) / 16) * 1024;
 }
 
-// Steps in blob order (chunks, kernel positions, 16-channel slices).
-void build_wide_layout(const Geom &g, const WidePlan &wp, const uint8_t *w, const Mask4 *m4,
-                       std::vector<uint8_t> &out) {
+// Bytes of the wide section: the bytes a wave may read past the weights hold
+// the stage table too (a u32 for at most kWidePieces * 256 slots).
+uint64_t wide_section_bytes(const Geom &g) {
+  static_assert(kWidePieces * 256 * 4 <= kWideTail, "the stage table fits the tail");
+  return wide_weight_bytes(g) + kWideTail;
+}
+
+// Steps in blob order (chunks, kernel positions, 16-channel slices); out holds
+// zeros.
+void build_wide_layout(const Geom &g, const WidePlan &wp, const uint8_t *w, const Mask4 *m4, uint8_t *out) {
   const int c16_total = (g.c_in + 15) / 16;
   const long stot = static_cast<long>(g.ks) * c16_total;
-  const size_t weights = wide_weight_bytes(g);
-  out.assign(weights, 0);
   std::vector<long> step_of(stot);   // [c16 slice][pos] -> step
   {
     long s = 0;
@@ -1557,30 +1583,45 @@ void build_wide_layout(const Geom &g, const WidePlan &wp, const uint8_t *w, cons
       for (int pos = 0; pos < g.ks; ++pos)
         for (int c = c0; c < std::min(c16_total, c0 + wp.c16); ++c) step_of[static_cast<long>(c) * g.ks + pos] = s++;
   }
+  // 32 filters x 16 channels at a time (their weights and fragments stay in
+  // the host's caches), a lane's 8 channels per store.
   const uint16_t *src = reinterpret_cast<const uint16_t *>(w);
-  uint16_t *dst = reinterpret_cast<uint16_t *>(out.data());
-  for (int m = 0; m < g.c_out; ++m)
-    for (int c = 0; c < g.c_in; ++c) {
-      const uint16_t *row = src + (static_cast<size_t>(m) * g.c_in + c) * g.ks;
-      const long lane = (m & 31) + 32 * ((c >> 3) & 1);
-      const long base = (m >> 5) * stot * 512 + lane * 8 + (c & 7);
-      const long *so = &step_of[static_cast<long>(c >> 4) * g.ks];
-      const uint8_t *mk = m4 ? m4->mask + (static_cast<size_t>(m / 4 / m4->gm4) * m4->Q + c / 4 / m4->gn4) * g.ks : nullptr;
-      for (int pos = 0; pos < g.ks; ++pos)
-        if (!mk || mk[pos]) dst[base + so[pos] * 512] = row[pos];
+  uint16_t *dst = reinterpret_cast<uint16_t *>(out);
+  for (int m0 = 0; m0 < g.c_out; m0 += 32)
+    for (int c16 = 0; c16 < c16_total; ++c16) {
+      const long *so = &step_of[static_cast<long>(c16) * g.ks];
+      uint16_t *frag = dst + (m0 >> 5) * stot * 512;
+      for (int m = m0; m < std::min(m0 + 32, g.c_out); ++m)
+        for (int c = c16 * 16; c < std::min(c16 * 16 + 16, g.c_in); c += 8) {
+          const int nc = std::min(8, g.c_in - c);
+          const uint16_t *rows = src + (static_cast<size_t>(m) * g.c_in + c) * g.ks;
+          uint16_t *to = frag + ((m & 31) + 32 * ((c >> 3) & 1)) * 8;
+          const uint8_t *mk[2] = {nullptr, nullptr};   // of channels c .. c + 3 and c + 4 .. c + 7
+          for (int j = 0; m4 && j < nc; j += 4)
+            mk[j / 4] = m4->mask + (static_cast<size_t>(m / 4 / m4->gm4) * m4->Q + (c + j) / 4 / m4->gn4) * g.ks;
+          for (int pos = 0; pos < g.ks; ++pos) {
+            uint16_t v[8] = {0};
+            if (nc == 8 && !m4) {
+              for (int j = 0; j < 8; ++j) v[j] = rows[j * g.ks + pos];
+            } else {
+              for (int j = 0; j < nc; ++j)
+                if (!m4 || mk[j / 4][pos]) v[j] = rows[j * g.ks + pos];
+            }
+            std::memcpy(to + so[pos] * 512, v, sizeof(v));
+          }
+        }
     }
   // Stage table: where each 16-byte slot of a halo buffer comes from.
   const int hh = (wp.bh - 1) * g.sh + g.kh, hw = (wp.bw - 1) * g.sw + g.kw, spr = wp.c16 * 2 + 1;
   const int ht = (wp.bt - 1) * g.st + g.kt;
-  for (int r = 0; r < ht * wp.hpp; ++r) {
-    const uint32_t t = r / wp.hpp, h = r % wp.hpp / wp.hwp, w2 = r % wp.hpp % wp.hwp;
-    for (int p = 0; p < spr; ++p) {
-      const bool real = static_cast<int>(h) < hh && static_cast<int>(w2) < hw && p < spr - 1;
-      const uint32_t e = real ? t | h << 9 | w2 << 18 | static_cast<uint32_t>(p) << 27 : ~0u;
-      out.insert(out.end(), reinterpret_cast<const uint8_t *>(&e), reinterpret_cast<const uint8_t *>(&e) + 4);
+  uint32_t *tab = reinterpret_cast<uint32_t *>(out + wide_weight_bytes(g));
+  for (int t = 0; t < ht; ++t)
+    for (int r = 0; r < wp.hpp; ++r) {
+      const uint32_t h = r / wp.hwp, w2 = r % wp.hwp;
+      const bool voxel = static_cast<int>(h) < hh && static_cast<int>(w2) < hw;
+      for (int p = 0; p < spr; ++p)
+        *tab++ = voxel && p < spr - 1 ? t | h << 9 | w2 << 18 | static_cast<uint32_t>(p) << 27 : ~0u;
     }
-  }
-  out.resize(std::max(out.size(), weights + kWideTail), 0);
 }
 
 // Assemble header + canonical + layout sections.  With out == nullptr only
@@ -1610,9 +1651,9 @@ Sections section_offsets(const Canon *c, int es, const Layout &L) {
   s.keep = off;
   off = align_up(off + L.keep.size() * 4, kAlign);
   s.a = off;
-  off = align_up(off + L.a.size(), kAlign);
+  off = align_up(off + L.a.size() + L.a_sized, kAlign);
   s.wide = off;
-  off = align_up(off + L.wide_a.size(), kAlign);
+  off = align_up(off + L.wide_bytes, kAlign);
   s.total = off;
   return s;
 }
@@ -1650,7 +1691,7 @@ void fill_info(const rt3d_conv3d_desc *d, const Canon *c, const Layout &L, const
   p.a_off = s.a;
   p.keep_off = s.keep;
   std::memcpy(info->plan, &p, sizeof(p));
-  if (!L.wide_a.empty()) {
+  if (L.wide_bytes) {
     WidePlan wp = L.wide;
     wp.a_off = s.wide;
     std::memcpy(reinterpret_cast<uint8_t *>(info->plan) + sizeof(p), &wp, sizeof(wp));
@@ -1658,7 +1699,7 @@ void fill_info(const rt3d_conv3d_desc *d, const Canon *c, const Layout &L, const
 }
 
 void write_blob(uint8_t *out, const rt3d_pack_info &info, const Canon *c, const uint8_t *w,
-                const rt3d_conv3d_desc *d, const Layout &L, const Sections &s) {
+                const rt3d_conv3d_desc *d, const Layout &L, const Sections &s, const Mask4 *m4) {
   std::memset(out, 0, s.total);
   std::memcpy(out, &info, sizeof(info));
   if (c) {
@@ -1691,7 +1732,8 @@ void write_blob(uint8_t *out, const rt3d_pack_info &info, const Canon *c, const 
   if (!L.items.empty()) std::memcpy(out + s.items, L.items.data(), L.items.size() * 4);
   if (!L.keep.empty()) std::memcpy(out + s.keep, L.keep.data(), L.keep.size() * 4);
   if (!L.a.empty()) std::memcpy(out + s.a, L.a.data(), L.a.size());
-  if (!L.wide_a.empty()) std::memcpy(out + s.wide, L.wide_a.data(), L.wide_a.size());
+  if (L.wide_bytes && L.wide.rgb) build_rgb_layout(geom_of(d), w, m4, out + s.wide);
+  else if (L.wide_bytes) build_wide_layout(geom_of(d), L.wide, w, m4, out + s.wide);
 }
 
 // 16-bit KGS mapping: pairs (2:4 sparse MFMA over 64-slot bricks) or the
@@ -1739,18 +1781,20 @@ int pair_width(const Geom &g, const Mask4 *m4) {
   return (v == 2 || v == 4) ? v : 1;
 }
 
-// Adds the wide layout where the planner wants one.
-void add_wide(const Geom &g, bool small, const uint8_t *w, const Mask4 *m4, Layout &L) {
+// Plans the wide layout where the planner wants one; write_blob builds it in
+// place (its size does not depend on the weights).
+void add_wide(const Geom &g, bool small, Layout &L) {
   if (small) {
     // (not where a tuning switch asks for a layout of the small-channel kernel)
     if (tune("wide") == 0 || tune("small_mfw") >= 0 || !rgb_shape(g).ok) return;
-    build_rgb_layout(g, w, m4, L.wide_a);
     L.wide.rgb = 1;
+    L.wide_bytes = static_cast<uint64_t>((g.c_out + 63) / 64) * rgb_shape(g).steps * 2048;
     return;
   }
-  if (!wide_wanted(g, small, m4)) return;
+  if (!wide_wanted(g, small)) return;
   L.wide = wide_tiling(g, 4);
-  if (L.wide.c16 > 0 && (g.c_in + 15) / 16 / L.wide.c16 < 4000) build_wide_layout(g, L.wide, w, m4, L.wide_a);
+  if (L.wide.c16 == 0 || (g.c_in + 15) / 16 / L.wide.c16 >= 4000) return;
+  L.wide_bytes = wide_section_bytes(g);
 }
 
 // Build everything for a KGS pack (w may be null when only sizing).
@@ -1773,40 +1817,27 @@ rt3d_status plan_kgs(const rt3d_conv3d_desc *d, const uint8_t *mask, const uint8
   const ItemPlan ip = item_plan(g, &m4, small);
   tl = ip.tl;
   if (tl.cc == 0) return fail(RT3D_ERR_UNSUPPORTED, "no voxel tiling fits in LDS for this layer");
-  static const uint8_t zero = 0;
-  const uint8_t *wsrc = w ? w : &zero;
-  if (!w) {
-    // Sizing only: build the layout from a weight source that is never
-    // dereferenced beyond the mask check by using an all-zero byte span.
-    // The layout size does not depend on weight values.
-  }
+  // The exact fp32 and the pair layouts are built to be sized, from weights
+  // that stand for any (a layout's size does not depend on their values).
+  std::vector<uint8_t> scratch;
+  auto weights = [&] {
+    if (!w) scratch.assign(static_cast<size_t>(g.c_out) * g.c_in * ks * g.es, 0);
+    return w ? w : scratch.data();
+  };
   if (g.es == 4) {
-    std::vector<uint8_t> scratch;
-    if (!w) {
-      // size-only pass: reuse the builders with a scratch weight tensor
-      scratch.assign(static_cast<size_t>(g.c_out) * g.c_in * ks * g.es, 0);
-      wsrc = scratch.data();
-    }
-    if (use_f32_union(g, c.nvals)) build_items_layout(g, tl, wsrc, &m4, L, false, 1);
-    else build_exact_f32_layout(g, tl, wsrc, &m4, L);
+    if (use_f32_union(g, c.nvals)) build_items_layout(g, tl, w, &m4, L, false, 1);
+    else build_exact_f32_layout(g, tl, weights(), &m4, L);
+  } else if (!small && use_block_pairs(g, &m4)) {
+    tl = choose_tiling(g, 64);
+    if (tl.cc == 0) return fail(RT3D_ERR_UNSUPPORTED, "no voxel tiling fits in LDS for this layer");
+    build_block_pairs_layout(g, tl, weights(), &m4, L);
+  } else if (!small && use_pairs(g, &m4)) {
+    tl = choose_tiling(g, 64);
+    if (tl.cc == 0) return fail(RT3D_ERR_UNSUPPORTED, "no voxel tiling fits in LDS for this layer");
+    build_pairs_layout(g, tl, weights(), &m4, L, pair_width(g, &m4));
   } else {
-    std::vector<uint8_t> scratch;
-    if (!w) {
-      scratch.assign(static_cast<size_t>(g.c_out) * g.c_in * ks * g.es, 0);
-      wsrc = scratch.data();
-    }
-    if (!small && use_block_pairs(g, &m4)) {
-      tl = choose_tiling(g, 64);
-      if (tl.cc == 0) return fail(RT3D_ERR_UNSUPPORTED, "no voxel tiling fits in LDS for this layer");
-      build_block_pairs_layout(g, tl, wsrc, &m4, L);
-    } else if (!small && use_pairs(g, &m4)) {
-      tl = choose_tiling(g, 64);
-      if (tl.cc == 0) return fail(RT3D_ERR_UNSUPPORTED, "no voxel tiling fits in LDS for this layer");
-      build_pairs_layout(g, tl, wsrc, &m4, L, pair_width(g, &m4));
-    } else {
-      build_items_layout(g, tl, wsrc, &m4, L, small, ip.mfw);
-      add_wide(g, small, wsrc, &m4, L);
-    }
+    build_items_layout(g, tl, w, &m4, L, small, ip.mfw);
+    add_wide(g, small, L);
   }
   return ok();
 }
@@ -2351,7 +2382,8 @@ rt3d_status rt3d_kgs_pack(const rt3d_conv3d_desc *d, const void *w_dense, const 
                 static_cast<unsigned long long>(s.total), static_cast<unsigned long long>(blob_bytes));
   rt3d_pack_info tmp;
   fill_info(d, &c, L, tl, s, vanilla, &tmp);
-  write_blob(static_cast<uint8_t *>(blob), tmp, &c, static_cast<const uint8_t *>(w_dense), d, L, s);
+  const Mask4 m4{mask, c.Q, d->kt * d->kh * d->kw, d->g_m / 4, d->g_n / 4};
+  write_blob(static_cast<uint8_t *>(blob), tmp, &c, static_cast<const uint8_t *>(w_dense), d, L, s, &m4);
   *info = tmp;
   return ok();
 }
@@ -2487,10 +2519,9 @@ rt3d_status rt3d_dense_pack_size(const rt3d_conv3d_desc *d, uint64_t *bytes) {
   const ItemPlan ip = item_plan(g, nullptr, small);
   const Tiling &tl = ip.tl;
   if (tl.cc == 0) return fail(RT3D_ERR_UNSUPPORTED, "no voxel tiling fits in LDS for this layer");
-  std::vector<uint8_t> scratch(static_cast<size_t>(g.c_out) * g.c_in * g.ks * g.es, 0);
   Layout L;
-  build_items_layout(g, tl, scratch.data(), nullptr, L, small, ip.mfw);
-  add_wide(g, small, scratch.data(), nullptr, L);
+  build_items_layout(g, tl, nullptr, nullptr, L, small, ip.mfw);
+  add_wide(g, small, L);
   *bytes = section_offsets(nullptr, g.es, L).total;
   return ok();
 }
@@ -2508,14 +2539,14 @@ rt3d_status rt3d_dense_pack(const rt3d_conv3d_desc *d, const void *w_dense, void
   if (tl.cc == 0) return fail(RT3D_ERR_UNSUPPORTED, "no voxel tiling fits in LDS for this layer");
   Layout L;
   build_items_layout(g, tl, static_cast<const uint8_t *>(w_dense), nullptr, L, small, ip.mfw);
-  add_wide(g, small, static_cast<const uint8_t *>(w_dense), nullptr, L);
+  add_wide(g, small, L);
   const Sections s = section_offsets(nullptr, g.es, L);
   if (blob_bytes < s.total)
     return fail(RT3D_ERR_BUFFER_TOO_SMALL, "blob needs %llu bytes, got %llu",
                 static_cast<unsigned long long>(s.total), static_cast<unsigned long long>(blob_bytes));
   rt3d_pack_info tmp;
   fill_info(d, nullptr, L, tl, s, false, &tmp);
-  write_blob(static_cast<uint8_t *>(blob), tmp, nullptr, nullptr, d, L, s);
+  write_blob(static_cast<uint8_t *>(blob), tmp, nullptr, static_cast<const uint8_t *>(w_dense), d, L, s, nullptr);
   *info = tmp;
   return ok();
 }

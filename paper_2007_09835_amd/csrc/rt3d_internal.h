@@ -109,7 +109,7 @@ struct ConvArgs {
 // chunk's 16-channel slices.
 // After the weights: the stage table, u32 per 16-byte slot of a halo buffer,
 // t | h << 9 | w << 18 | piece << 27 in the halo, all ones for padding.  The
-// section ends kWideTail bytes behind the weights at the earliest.
+// section ends kWideTail bytes behind the weights.
 struct WidePlan {
   uint64_t a_off;
   uint8_t bt, bh, bw;      // output brick
@@ -135,6 +135,7 @@ struct WideArgs : ConvArgs {
 };
 
 constexpr int kWideSteps = 128;   // most K-steps of one part and chunk
+constexpr int kWidePieces = 11;   // direct loads per staging lane and chunk (at most 44 KB)
 constexpr int kWideRing = 6;      // weight fragments in flight per row (steps); even
 constexpr int kWideTail = (kWideRing - 1) * 7 * 1024;  // bytes a wave may read past the weights
 

@@ -1074,8 +1074,6 @@ __device__ __forceinline__ void wide_barrier() {
   asm volatile("" ::: "memory");
 }
 
-constexpr int kWidePieces = 11;  // direct loads per staging lane and chunk (at most 44 KB)
-
 template <typename T, int FM, int FN, int WK>
 __global__ __launch_bounds__(512, 2) void wide_kernel(WideArgs a) {
   using V8 = std::conditional_t<std::is_same_v<T, __bf16>, bf16x8, f16x8>;
