@@ -1064,6 +1064,18 @@ __device__ __forceinline__ void load_to_lds(const uint8_t *src, uint8_t *lds) {
       (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
 }
 
+// Zeros 16 bytes of LDS beside direct loads in flight to other places.  As an
+// ordinary store the compiler makes it wait for every direct load of the wave,
+// which serialised the loads of bricks at the clip's border: 336->53 1x3x3
+// stride 2 on 29x7x16x16 took 65.2 us, 29.2 without the waits.  The barrier that
+// ends the chunk waits for it.
+__device__ __forceinline__ void zero_lds(uint8_t *lds) {
+  const uint32_t at = static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void *)lds));
+  const u32x4 zero = {0, 0, 0, 0};
+  asm volatile("ds_write_b128 %0, %1" : : "v"(at), "v"(zero) : "memory");
+}
+
 // Workgroup barrier of the wide kernel.  Every LDS access of the wave is done
 // first; with VM its vector-memory loads (direct-to-LDS writes) are too.
 template <bool VM>
@@ -1133,8 +1145,7 @@ __global__ __launch_bounds__(512, 2) void wide_kernel(WideArgs a) {
           if (k * 256 >= npieces) break;
           if (off[k] != ~0u) load_to_lds(src + off[k], dst + (k * 256 + (wave - 4) * 64) * 16);
           if ((pads >> k) & 1u) {
-            if (code[k] != ~0u && off[k] == ~0u)
-              *reinterpret_cast<uint4 *>(dst + (st + k * 256) * 16) = make_uint4(0, 0, 0, 0);
+            if (code[k] != ~0u && off[k] == ~0u) zero_lds(dst + (st + k * 256) * 16);
           }
         }
         buf ^= 1;
@@ -1148,7 +1159,7 @@ __global__ __launch_bounds__(512, 2) void wide_kernel(WideArgs a) {
           load_to_lds(src + off[k], dst + (k * 256 + (wave - 4) * 64) * 16);
         else if (code[k] != ~0u && (off[k] == ~0u || (c & ~15) < a.c_in))
           // padding, or the upper half of the last 16-channel slice
-          *reinterpret_cast<uint4 *>(dst + (st + k * 256) * 16) = make_uint4(0, 0, 0, 0);
+          zero_lds(dst + (st + k * 256) * 16);
       }
       // A channel count that is not a multiple of 8: the last piece's extra
       // channels (another layer's, or padding of the pitch) become zeros.
