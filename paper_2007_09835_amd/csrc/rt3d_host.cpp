@@ -1337,6 +1337,8 @@ constexpr double kWideLoad = 5.8, kWideLoadFree = 4817, kWideChunk = 670, kWideS
 // kWideSecondLaunch: what a split's second launch costs a layer that the item
 // kernel runs in one (small eager calls are bound by launches: 64->64 3x3x3 on
 // 4x14x14 took 10.5 us unsplit on the item kernel and 13.5 split on this one).
+// Of 325 layers timed in graphs, 16 could split here where the item kernel does
+// not: one of them was the faster for it (115->96 1x3x3 on 4x24x24, 13.1 -> 11.8).
 constexpr double kWideSecondLaunch = 10000;
 constexpr double kNoLimit = 1e300;
 constexpr double kWideReduceStart = 4700, kWidePartialBytes = 0.63;
@@ -2009,9 +2011,17 @@ WidePlan wide_plan_of(const rt3d_pack_info *info) {
 // not a multiple of 8 channels (the staging loads whole 16-byte pieces), a
 // blob that ends less than kWideTail bytes behind the weights, a batch item of
 // 4 GiB or more (32-bit halo offsets), or an item-kernel launch that is modelled
-// faster.  The item kernel's model was fitted like the wide
-// one's (its own cycles x 0.73 plus 1.06 us per million outputs, 10% mean
-// error); the 5% margin keeps the item kernel where the two are close.
+// faster.  The item kernel's model (its own cycles x 0.677, 1.34 us
+// per million outputs, 0.47 us per million bytes of partial sums and 0.84 us)
+// was fitted to 325 layers of the C3D, R(2+1)D and S3D stacks at batch 1 to 8
+// and random ones of their range (13% rms error; the wide one's is 10% there).
+// kWideOver is what the wide kernel takes beyond its model where the two meet
+// (calls of 8-9 us); the margin keeps the item kernel where they are close.  Of
+// the 325 the rule sends 197 to the wide kernel, and 3 are over 3% slower than
+// on the item kernel (8 without kWideOver: pointwise layers, 7.6 us against 8.2);
+// the mean is 12.3% faster.  Pooled layers of few channels, whose epilogue
+// is cheaper than the model has it, stay on the item kernel up to 10% too long
+// (64->128 3x3x3 + 2x2x2 pool at batch 8: 181 us against 163).
 WideLaunch plan_wide(const rt3d_conv3d_desc *d, const Geom &g, const rt3d_pack_info *info, uint64_t ws_cap,
                      const Launch &item_launch, const Tune &tuned) {
   const WidePlan wp = wide_plan_of(info);
@@ -2022,13 +2032,15 @@ WideLaunch plan_wide(const rt3d_conv3d_desc *d, const Geom &g, const rt3d_pack_i
   if (info->packed_bytes < wp.a_off + wide_weight_bytes(g) + kWideTail) return none;
   if (static_cast<double>(g.t) * g.h * g.w * x_pitch * 2 >= 4.29e9) return none;
   const double outputs = static_cast<double>(g.n) * g.to * g.ho * g.wo * g.c_out;
-  const double item = 0.73 * item_launch.cycles + 2383e-6 * outputs;
+  const double item = 0.677 * item_launch.cycles + 3.01e-3 * outputs +
+                      1.05e-3 * static_cast<double>(item_launch.ws_bytes) + 1890;
+  constexpr double kMargin = 1.05, kWideOver = 1400;
   // (a tuning switch may ask for shapes that the model would not take)
   const bool free_choice = tuned("wide") != 1;
-  const double limit = tuned.on ? kNoLimit : 1.000001 * item / 1.05;
+  const double limit = tuned.on ? kNoLimit : 1.000001 * (item / kMargin - kWideOver);
   const WideLaunch L = best_wide(g, wp, std::min<uint64_t>(ws_cap, kScratchBytes), device_cus(), tuned("splits"),
                                  tuned("wide_fm"), tuned("wide_wm"), item_launch.splits > 1 ? 0 : kWideSecondLaunch, limit);
-  return L.fm == 0 || (free_choice && item < 1.05 * L.cycles) ? none : L;
+  return L.fm == 0 || (free_choice && item < kMargin * (L.cycles + kWideOver)) ? none : L;
 }
 
 // Bytes of the item kernel's weight section (the wide section, when there is
