@@ -52,8 +52,8 @@
  *     saves any, 0 = never), wide=0 (no wide layout; so does any of the keys
  *     above but the small_ ones).  Launch-time
  *     keys change the launch of a forward call: splits=N (input-channel
- *     splits), wg_order=0|1 (workgroup order), wide=1 (the wide kernel
- *     wherever the blob and the input allow it), wide_fm=1|2 (its 32-filter
+ *     splits), wg_order=0|1 (workgroup order), wide=1 (the wide and RGB kernels
+ *     wherever the blob and the input allow them; wide=0 at a launch: no RGB kernel), wide_fm=1|2 (its 32-filter
  *     rows per wave) and wide_wm=1|2|4 (its waves along the filters).  Results stay within the
  *     documented accuracy under every setting.
  *   - Errors: all arguments are validated before anything is launched; on

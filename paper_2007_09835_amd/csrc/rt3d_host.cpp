@@ -2019,7 +2019,7 @@ WidePlan wide_plan_of(const rt3d_pack_info *info) {
 // (calls of 8-9 us); the margin keeps the item kernel where they are close.  Of
 // the 325 the rule sends 197 to the wide kernel, and 3 are over 3% slower than
 // on the item kernel (8 without kWideOver: pointwise layers, 7.6 us against 8.2);
-// the mean is 12.3% faster.  Pooled layers of few channels, whose epilogue
+// the mean is 12.2% faster.  Pooled layers of few channels, whose epilogue
 // is cheaper than the model has it, stay on the item kernel up to 10% too long
 // (64->128 3x3x3 + 2x2x2 pool at batch 8: 181 us against 163).
 WideLaunch plan_wide(const rt3d_conv3d_desc *d, const Geom &g, const rt3d_pack_info *info, uint64_t ws_cap,
@@ -2078,12 +2078,20 @@ int wide_order(const Geom &g, const WidePlan &wp, const WideLaunch &L, const Tun
 }
 
 // Layers with up to 4 input channels: the RGB kernel, except where a residual
-// is added or an output voxel's filters are not whole 16-byte words (the
-// small-channel kernel).
-bool takes_rgb(const rt3d_conv3d_desc *d, const WidePlan &wp, const Tune &tuned) {
+// is added, an output voxel's filters are not whole 16-byte words or the call
+// has too few bricks (the small-channel kernel).  A brick's halo and the weights
+// of every step are staged before the first multiplication, which the small-
+// channel kernel's finer bricks hide sooner: 1x7x7 stride 2 (14 steps) took 8.5
+// us there and 11.1 here on 8 bricks, 9.7 and 11.4 on 28, 11.1 and 10.9 on 96;
+// 3x3x3 (9 steps) 7.9 and 8.5 on 28, 8.2 and 7.7 on 56.  With fewer steps the
+// RGB kernel was the faster one on every size (one brick of 1x1x1: 7.3, 6.1).
+bool takes_rgb(const rt3d_conv3d_desc *d, const Geom &g, const WidePlan &wp, const Tune &tuned) {
   const int y_pitch = d->y_c_total != 0 ? d->y_c_total : d->c_out;
-  return wp.a_off != 0 && wp.rgb && !(d->flags & RT3D_RESIDUAL) && tuned("wide") != 0 &&
-         (d->c_out | y_pitch | d->y_c_off) % 8 == 0;
+  if (wp.a_off == 0 || !wp.rgb || (d->flags & RT3D_RESIDUAL) || (d->c_out | y_pitch | d->y_c_off) % 8 != 0) return false;
+  if (tuned("wide") >= 0) return tuned("wide") != 0;
+  const int steps = rgb_shape(g).steps;
+  const long bricks = static_cast<long>(g.n) * ((g.to + 3) / 4) * ((g.ho + 3) / 4) * ((g.wo + 31) / 32);
+  return steps < 9 || bricks >= 5 * steps;
 }
 
 rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, const void *blob,
@@ -2164,7 +2172,7 @@ rt3d_status run_conv(const rt3d_conv3d_desc *d, const rt3d_pack_info *info, cons
   if (static_cast<long>(a.n) * a.nbt * a.nbh * a.nbw * a.ntg * a.splits >= (1L << 24))
     return fail(RT3D_ERR_UNSUPPORTED, "layer needs 2^24 or more workgroups");
   int e;
-  if (takes_rgb(d, wp, tuned)) {
+  if (takes_rgb(d, g, wp, tuned)) {
     const RgbShape r = rgb_shape(g);
     WideArgs ra{};
     static_cast<ConvArgs &>(ra) = a;
@@ -2473,7 +2481,7 @@ rt3d_status rt3d_conv3d_launch_info(const rt3d_conv3d_desc *d, const rt3d_pack_i
   const Geom g = geom_of(d);
   const Launch L = plan_launch(d, g, p, info->variant, workspace_bytes, tuned);
   const WideLaunch W = plan_wide(d, g, info, workspace_bytes, L, tuned);
-  if (takes_rgb(d, wp, tuned))
+  if (takes_rgb(d, g, wp, tuned))
     *out = {RT3D_KERNEL_RGB, 4, 4, 32, d->c_in, 64, 1, 1, 1, 0, 0};
   else if (W.fm > 0)
     *out = {RT3D_KERNEL_WIDE, wp.bt, wp.bh, wp.bw, wp.c16 * 16, 32 * W.fm, W.wm, W.wk, W.splits, wide_order(g, wp, W, tuned), W.ws_bytes};

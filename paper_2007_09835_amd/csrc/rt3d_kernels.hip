@@ -3251,13 +3251,19 @@ int launch_kgs_exact_f32(const ConvArgs &a, void *stream) {
 // Outputs per thread of maxpool_run_kernel for this pool, 0 when it does not
 // apply (windows other than 3x3x3 and 1x3x3, strides other than 1 or 2 along
 // w).  Seven along w where that still gives each SIMD four waves, four where
-// that gives it one; smaller pools are bound by latency and keep a thread per
-// output (S3D m5, 2x7x7x832 at batch 1).
+// that gives it one (one and a half for 1x3x3 windows at stride 2, which share
+// the fewest columns: 8x3x56x19x312 7.2 -> 8.9 us, 1x8x56x56x192 fp32 6.9 -> 7.5
+// at one); smaller pools are bound by latency and keep a thread per output (S3D
+// m5, 2x7x7x832 at batch 1).  Of 200 random pools that take runs, 31 were over
+// 3% slower with them than with a thread per output, all 1x3x3 or fp32 at stride 2
+// (at most 1.45x); the fp32 1x3x3 ones were 0.45-1.45x, 0.93x on average, in no
+// order of size, channels or stride that a rule could follow.
 int pool_run(const PoolArgs &p, long outs) {
   if (!((p.kt == 3 || p.kt == 1) && p.kh == 3 && p.kw == 3 && (p.sw == 1 || p.sw == 2))) return 0;
   const long lines = outs / p.wo * p.cv;
+  const long least = p.kt == 1 && p.sw == 2 ? 98304 : 65536;
   for (const int r : {7, 4})
-    if (lines * ((p.wo + r - 1) / r) >= (r == 7 ? 262144 : 65536)) return r;
+    if (lines * ((p.wo + r - 1) / r) >= (r == 7 ? 262144 : least)) return r;
   return 0;
 }
 

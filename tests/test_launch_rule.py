@@ -112,3 +112,17 @@ def test_smallest_pointwise_layers_stay_on_the_item_kernel(c_in, c_out, thw, k):
     it (7.5-8.9 us on the item kernel, 8.3-9.5 on the wide one)."""
     d, info = pack(c_in, c_out, thw, k)
     assert rt3d.rt3d_conv3d_launch_info(d, info).kernel == rt3d.KERNELS.index("item")
+
+
+@pytest.mark.parametrize("thw,k,stride,pad,n,kernel", [
+    ((8, 28, 28), (1, 7, 7), (1, 2, 2), (0, 3, 3), 1, "small"),    # 8 bricks of 14 steps
+    ((16, 224, 224), (1, 7, 7), (1, 2, 2), (0, 3, 3), 1, "rgb"),
+    ((8, 56, 12), (3, 3, 3), (1, 1, 1), (1, 1, 1), 1, "small"),    # 28 bricks of 9 steps
+    ((4, 56, 36), (3, 3, 3), (1, 1, 1), (1, 1, 1), 2, "rgb"),      # 56
+    ((3, 4, 12), (1, 3, 3), (1, 1, 1), (0, 1, 1), 1, "rgb")])
+def test_few_bricks_of_many_steps_stay_on_the_small_channel_kernel(thw, k, stride, pad, n, kernel, monkeypatch):
+    d = rt3d.make_desc(n, 3, 64, thw, k, stride, pad, dtype="bf16")
+    _, info = rt3d.rt3d_dense_pack(d, torch.zeros((64, 3, *k), dtype=torch.bfloat16))
+    assert rt3d.KERNELS[rt3d.rt3d_conv3d_launch_info(d, info).kernel] == kernel
+    monkeypatch.setenv("RT3D_TUNE", "wide=1")
+    assert rt3d.KERNELS[rt3d.rt3d_conv3d_launch_info(d, info).kernel] == "rgb"
