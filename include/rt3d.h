@@ -228,7 +228,8 @@ rt3d_status rt3d_conv3d_launch_info(const rt3d_conv3d_desc *desc, const rt3d_pac
  * RT3D_RESIDUAL is set.  y must not overlap x, residual or the blob.  Work
  * skipped: a (4-channel block, kernel position) item that no kernel group
  * of a wave's filter tile keeps is never read or multiplied (so a vanilla-
- * pruned group costs nothing when its tile-mates prune the same channels).
+ * pruned group costs nothing when its tile-mates prune the same channels),
+ * except by the wide and RGB kernels below.
  * How a kept item is multiplied depends on the mapping chosen at pack time:
  * the exact fp32 kernel issues one 4x4 MFMA per kept (group, item); the
  * union mappings (16-bit, and fp32 for layers too small to be bound by
@@ -238,7 +239,11 @@ rt3d_status rt3d_conv3d_launch_info(const rt3d_conv3d_desc *desc, const rt3d_pac
  * 16-bit pair mapping packs two items whose kept groups
  * are disjoint into one 2:4 sparse MFMA slot and streams kept weights only;
  * the wide 16-bit kernel, taken where it is modelled faster, multiplies every
- * (16-channel slice, position) of a 64-filter tile, pruned weights as zeros.
+ * (16-channel slice, position) of a 64-filter tile, pruned weights as zeros,
+ * and so does the RGB kernel (16-bit, c_in <= 4) with every kernel position.
+ * Blobs of 16-bit layers with 16 or more input channels therefore hold a dense
+ * copy of the weights beside the kept ones (C3D conv3b at 3x: 9.5 MB, 4.6 of
+ * them kept weights and their index).
  * Asynchronous on `stream`.  Per-call limits (RT3D_ERR_UNSUPPORTED,
  * checked before any launch; the same for rt3d_conv3d_dense_fwd): fewer
  * than 2^24 output voxels and 2^24 workgroups, and for layers packed onto
@@ -289,7 +294,8 @@ rt3d_status rt3d_conv3d_dense_fwd(const rt3d_conv3d_desc *desc, const rt3d_pack_
  * windows with padding): channels-last x [n][t][h][w][c] -> y
  * [n][to][ho][wo][c], to = (t + 2 pt - kt) / st + 1 (floor), likewise ho, wo.
  * Padded positions take no part in the max; padding is at most half the
- * window (so every window holds input voxels).  Asynchronous on `stream`. */
+ * window (so every window holds input voxels).  A window whose maximum is zero
+ * gives a zero of either sign that it holds.  Asynchronous on `stream`. */
 rt3d_status rt3d_maxpool3d_fwd(int32_t n, int32_t c, int32_t t, int32_t h, int32_t w,
                                int32_t kt, int32_t kh, int32_t kw,
                                int32_t st, int32_t sh, int32_t sw,

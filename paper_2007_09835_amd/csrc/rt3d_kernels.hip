@@ -2553,7 +2553,8 @@ __global__ __launch_bounds__(256) void maxpool_kernel(const T *__restrict__ x, T
 // outside the input are clamped to the border voxel, which lies in the same
 // window (padding is at most half the window), so no load is conditional.
 // NaN as in maxpool_kernel: a window's first voxel decides, others are
-// skipped.
+// skipped.  Zeros of both signs are equal: which one a window of them gives
+// depends on the order of the comparisons.
 template <typename T, int VEC, int KT, int KH, int SW, int R>
 __global__ __launch_bounds__(256) void maxpool_run_kernel(const T *__restrict__ x, T *__restrict__ y,
                                                           PoolArgs p) {
@@ -3254,10 +3255,10 @@ int launch_kgs_exact_f32(const ConvArgs &a, void *stream) {
 // that gives it one (one and a half for 1x3x3 windows at stride 2, which share
 // the fewest columns: 8x3x56x19x312 7.2 -> 8.9 us, 1x8x56x56x192 fp32 6.9 -> 7.5
 // at one); smaller pools are bound by latency and keep a thread per output (S3D
-// m5, 2x7x7x832 at batch 1).  Of 200 random pools that take runs, 31 were over
-// 3% slower with them than with a thread per output, all 1x3x3 or fp32 at stride 2
-// (at most 1.45x); the fp32 1x3x3 ones were 0.45-1.45x, 0.93x on average, in no
-// order of size, channels or stride that a rule could follow.
+// m5, 2x7x7x832 at batch 1).  Of 200 pools timed, 28 were over 3% slower with
+// runs than with a thread per output, all of 1x3x3 windows or fp32 at stride 2;
+// the fp32 1x3x3 ones took 0.45-1.45x, 0.93x on average, in no order of size,
+// channels or stride that a rule could follow.
 int pool_run(const PoolArgs &p, long outs) {
   if (!((p.kt == 3 || p.kt == 1) && p.kh == 3 && p.kw == 3 && (p.sw == 1 || p.sw == 2))) return 0;
   const long lines = outs / p.wo * p.cv;
