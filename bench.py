@@ -253,6 +253,20 @@ def _copy_calibration(torch, mib):
     return n * 4
 
 
+def launch_of(fn, conv, batch):
+    """The launch that a layer call (Stack.layer_calls) makes, with the
+    workspace it has."""
+    from paper_2007_09835_amd import rt3d
+    _, inp, _, out = fn.__defaults__
+    d = conv.desc_for(batch)
+    if inp.shape[-1] != d.c_in:
+        d.x_c_total = inp.shape[-1]
+    if out.shape[-1] != d.c_out:
+        d.y_c_total = out.shape[-1]
+    ws = conv.workspace(batch)
+    return rt3d.rt3d_conv3d_launch_info(d, conv.info, 0 if ws is None else 4 * ws.numel())
+
+
 def profile_stack(args, torch, stream):
     """Every conv of the stack launched --layer-reps times back to back (its
     split reduction after each launch when it splits), layer after layer,
@@ -260,7 +274,7 @@ def profile_stack(args, torch, stream):
     The manifest lists, per layer, the dispatches of one launch and the
     algorithmic FLOPs and bytes, so a summary can attribute rocprofv3's
     per-dispatch rows to layers by their order."""
-    from paper_2007_09835_amd import synth
+    from paper_2007_09835_amd import rt3d, synth
     from paper_2007_09835_amd.stack import make_stack
     st = make_stack(args.net, args.batch, args.dtype, args.mode, args.rate,
                     fuse_pool=not args.separate_pool, group=group_of(args))
@@ -270,12 +284,14 @@ def profile_stack(args, torch, stream):
                .permute(0, 2, 3, 4, 1).contiguous().cuda())
     layers = []
     for (l, fn), conv in zip(st.layer_calls(), st.convs):
-        split = conv.workspace(args.batch) is not None
+        launch = launch_of(fn, conv, args.batch)
+        split = launch.splits > 1
         roof = layer_roofline(l, conv, args.batch, 1.0)
-        i32 = [int(v) for v in __import__("numpy").frombuffer(bytes(conv.info.plan), dtype="int32")[:11]]
         layers.append({"layer": l.name, "kgs": conv.sparse, "dispatches": 2 if split else 1,
-                       "variant": int(conv.info.variant), "brick": i32[:3], "slots": i32[8],
-                       "mfw": i32[10], "kept_flops": roof["flops"], "bytes": roof["bytes"],
+                       "variant": int(conv.info.variant), "kernel": rt3d.KERNELS[launch.kernel],
+                       "brick": [launch.bt, launch.bh, launch.bw], "rows": launch.rows, "wm": launch.wm,
+                       "wk": launch.wk, "splits": launch.splits, "chunk": launch.chunk,
+                       "kept_flops": roof["flops"], "bytes": roof["bytes"],
                        "dense_flops": 2.0 * l.dense_macs(args.batch)})
     st.forward()
     torch.cuda.synchronize()
@@ -372,12 +388,14 @@ def summarize_profile(args):
         mfma = a.get("SQ_INSTS_MFMA", 0.0)
         gui = a.get("GRBM_GUI_ACTIVE", 1.0)
         util = 100.0 * a.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0) / max(gui / 8.0 * 1024.0, 1.0)
-        # 16x16x32 (16-bit) MFMAs: 16384 FLOP each; 16x16x4 f32: 2048; 4x4x1 f32 (x16 blocks): 512
-        per = {"bf16": 16384.0, "f16": 16384.0, "f32": 2048.0}[man["dtype"]]
+        # 16x16x32 (16-bit) MFMAs: 16384 FLOP each, the wide and RGB kernels' 32x32x16
+        # 32768; 16x16x4 f32: 2048; 4x4x1 f32 (x16 blocks): 512
+        per = 2048.0 if man["dtype"] == "f32" else 32768.0 if l["kernel"] in ("wide", "rgb") else 16384.0
         exec_ratio = mfma * per / l["kept_flops"] if l["kept_flops"] else 0.0
         t = (conv_us + red_us) * 1e-6
         frac = max(l["kept_flops"] / (peak * 1e12), l["bytes"] / (HBM_GBPS * 1e9)) / t
-        plan = "v%d %dx%dx%d/%d mfw%d" % (l["variant"], *l["brick"], l["slots"], l["mfw"])
+        plan = "%s v%d %dx%dx%d rows%d m%dk%d c%d s%d" % (
+            l["kernel"], l["variant"], *l["brick"], l["rows"], l["wm"], l["wk"], l["chunk"], l["splits"])
         lines.append("| %s | %s | %s | %.2f | %.2f | %.2f | %.2f | %.1f | %.2f | %.1f | %.2f | %.2f | %.3f |"
                      % (l["layer"], "KGS" if l["kgs"] else "dense", plan, conv_us, red_us,
                         (fb + wb) / 1e6, l["bytes"] / 1e6, util, exec_ratio,

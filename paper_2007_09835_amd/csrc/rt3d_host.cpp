@@ -1428,9 +1428,9 @@ WideLaunch best_wide(const Geom &g, const WidePlan &wp, uint64_t ws_cap, long cu
 // waste few slots, each with the pitch padding of the fewest LDS conflicts,
 // the launch model picks (a conflict costs about 4% of a step: the reads use
 // a quarter of the LDS rate).
-WidePlan wide_tiling(const Geom &g, int fn) {
+WidePlan wide_tiling(const Geom &g) {
   WidePlan best{};
-  const int slots = 32 * fn, c16_total = (g.c_in + 15) / 16;
+  const int slots = 128, c16_total = (g.c_in + 15) / 16;
   auto each_brick = [&](auto &&f) {
     for (int bw = g.qw; bw <= std::max(g.qw, std::min(g.wo, slots)); bw += g.qw)
       for (int bh = g.qh; bh <= std::max(g.qh, std::min(g.ho, slots / bw)); bh += g.qh)
@@ -1463,7 +1463,6 @@ WidePlan wide_tiling(const Geom &g, int fn) {
     wp.bt = static_cast<uint8_t>(bt);
     wp.bh = static_cast<uint8_t>(bh);
     wp.bw = static_cast<uint8_t>(bw);
-    wp.fn = static_cast<uint8_t>(fn);
     // Times without conflicts first: the pitches are searched for bricks that
     // can still win only.  (1.000001: the factor below may round to less than 1)
     double cycles[9];
@@ -1794,7 +1793,7 @@ void add_wide(const Geom &g, bool small, Layout &L) {
     return;
   }
   if (!wide_wanted(g, small)) return;
-  L.wide = wide_tiling(g, 4);
+  L.wide = wide_tiling(g);
   if (L.wide.c16 == 0 || (g.c_in + 15) / 16 / L.wide.c16 >= 4000) return;
   L.wide_bytes = wide_section_bytes(g);
 }

@@ -115,7 +115,7 @@ struct WidePlan {
   uint8_t bt, bh, bw;      // output brick
   uint8_t c16;             // 16-channel slices per chunk
   uint16_t hwp, hpp;       // halo pitches in voxels: per row of w, per plane of (h, w)
-  uint8_t fn;              // 32-slot voxel fragments per brick
+  uint8_t unused;
   uint8_t rgb;             // 1: the RGB kernel's weights instead (c_in <= 4): [64 filters][step]
                            // [32-filter row][lane][8], steps over kernel rows and groups of four
                            // w taps; bricks are 4x4x32, the geometry fields are unused

@@ -1561,7 +1561,7 @@ __global__ __launch_bounds__(512, 2) void wide_kernel(WideArgs a) {
 // written in 16-byte words.  One barrier per brick.
 //
 // Against the small-channel kernel below, bf16 3 -> 64 3x3x3 + 1x2x2 pool on
-// 16x112x112: 19.6 -> 11.8 us (1 clip), 59.5 -> 31.1 (4), 424 -> 191 (32).
+// 16x112x112: 19.6 -> 11.8 us (1 clip), 59.4 -> 29.3 (4), 424 -> 191 (32).
 // It is bound by vector and LDS work beside the MFMAs (348 TFLOP/s dense at 32
 // clips): a first version with that kernel's epilogue (2-byte-guarded stores,
 // bias and ReLU before the window maximum) took 55 us at 4 clips.
