@@ -615,7 +615,8 @@ struct SplitModel {
     constexpr double kFixed = 12000, kReduce = 9600, kShare = 0.2, kPartialBytesPerCycle = 4200;
     const long n = wgs * s;
     const long per_cu = s > 1 ? per_cu_split : per_cu_whole;
-    const long per = std::min<long>((n + cus - 1) / cus, per_cu);          // workgroups per CU at once
+    // workgroups per CU at once (none in an empty batch)
+    const long per = std::max<long>(1, std::min<long>((n + cus - 1) / cus, per_cu));
     const long rounds = (n + cus * per - 1) / (cus * per);
     return rounds * (kFixed + ((nchunks + s - 1) / s) * chunk_cycles *
                                   (1.0 + kShare * static_cast<double>(per - 1))) +

@@ -126,3 +126,14 @@ def test_few_bricks_of_many_steps_stay_on_the_small_channel_kernel(thw, k, strid
     assert rt3d.KERNELS[rt3d.rt3d_conv3d_launch_info(d, info).kernel] == kernel
     monkeypatch.setenv("RT3D_TUNE", "wide=1")
     assert rt3d.KERNELS[rt3d.rt3d_conv3d_launch_info(d, info).kernel] == "rgb"
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("c_in", [3, 12, 64, 512])
+def test_an_empty_batch_needs_no_workspace(c_in, dtype):
+    w = torch.zeros((64, c_in, 3, 3, 3), dtype={"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype])
+    d = rt3d.make_desc(1, c_in, 64, (4, 8, 8), dtype=dtype)
+    _, info = rt3d.rt3d_dense_pack(d, w)
+    d.n = 0
+    assert rt3d.rt3d_conv3d_workspace_size(d, info) == 0
+    assert rt3d.rt3d_conv3d_launch_info(d, info).workspace_bytes == 0
